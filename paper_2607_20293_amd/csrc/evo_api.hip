@@ -679,6 +679,8 @@ static int denoise_impl(evo_policy* p, int32_t batch, const float* obs_cond, con
     kp.L = s.L; kp.A = s.A; kp.n_obs = s.n_obs; kp.obs_dim = s.obs_dim; kp.obs_pad = p->obs_pad;
     kp.T = s.T; kp.clip = s.clip; kp.n_tiles = ps.n_tiles;
     kp.raw = p->d_raw; kp.pk = p->d_pk; kp.loff = p->d_loff; kp.poff = p->d_poff; kp.pk_obs = p->pk_obs;
+    kp.pk_layers = p->poff_h[0].qkv;
+    kp.raw_layers = (uint32_t)p->wo.layer[0].ln1_g;
     const WeightOffsets& wo = p->wo;
     kp.W_in = (uint32_t)wo.W_in; kp.b_in = (uint32_t)wo.b_in; kp.P_act = (uint32_t)wo.P_act;
     kp.b_obs = (uint32_t)wo.b_obs; kp.P_mem = (uint32_t)wo.P_mem; kp.lnf_g = (uint32_t)wo.lnf_g;
@@ -956,8 +958,8 @@ int evo_debug_read_cache(evo_policy* p, int32_t unit, int32_t sample, float* hos
       const int row = slot * s.H + i, rb = row / 16, rr = row % 16;
       for (int col = 0; col < d; ++col) {
         const int cbk = col / 16, w = cbk / CBW, c = cbk % CBW;
-        const int lane = (col % 16) + 16 * (rr / 4);
-        host_dst[(size_t)i * d + col] = buf[((size_t)((w * RB + rb) * CBW + c) * 64 + lane) * 4 + rr % 4];
+        const int lane = rr + 16 * (col % 16 / 4);
+        host_dst[(size_t)i * d + col] = buf[((size_t)((w * RB + rb) * CBW + c) * 64 + lane) * 4 + col % 4];
       }
     }
     return EVO_OK;

@@ -7,7 +7,12 @@
 //
 //  * The residual stream h of the tile lives in registers, laid out as the
 //    accumulator fragments of 16x16 MFMA tiles (each wave owns a fixed set
-//    of 16-column blocks of d).
+//    of 16-column blocks of d).  Every product is formed transposed (weights
+//    as the first MFMA operand, activations as the second), so a lane holds
+//    four consecutive columns of ONE row: row statistics are sums inside the
+//    lane plus two lane swaps, operands go to LDS as one wide store per
+//    block, and a product's result can feed the next fp32 product straight
+//    from its registers (attention probabilities, the head, the sampler).
 //  * The schedule arrives as per-step unit bitmasks {evaluate, reuse,
 //    store}.  Cacheable units (Sec. 3.1: SA, CA, FFN residual branches) are
 //    evaluated only where the schedule says so (Eq. 1); a refreshed residual
@@ -36,10 +41,10 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint64_t kMergedBit = 1ull << 63;
 constexpr int kMaskEntries = 341;  // (T x samples per tile) entries of 3 x u64 in LDS (8 KiB)
-constexpr int kMaxLayers = 21;     // 3L <= 63 units (one 64-bit mask per step)
 
 // float -> bfloat16 bits, round to nearest even: gfx950's conversion
 // instruction (v_cvt_pk_bf16_f32), two values at a time where possible
@@ -70,25 +75,25 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// 16x16 tile of q · kᵀ over a DH-long dot product on fp32 MFMA.  The K order
+// 16x16 tile of k · qᵀ over a DH-long dot product on fp32 MFMA: lane holds
+// the scores of query lane % 16 with keys 4 (lane / 16) .. + 3.  The K order
 // is permuted (any bijection of k works when both operands use it): lane
 // group lq takes k = 16·lq + j at step j, so each lane reads 16 contiguous
 // floats of its row (four 16-byte LDS reads) instead of 16 strided ones, and
 // four independent accumulators shorten the dependent MFMA chain.
 template <int DH>
-__device__ __forceinline__ f32x4 qk_tile(const float* qrow, const float* krow, bool kvalid, int lq) {
+__device__ __forceinline__ f32x4 qk_tile(const float* qrow, const float* krow, int lq) {
   static_assert(DH % 64 == 0 || DH == 32, "head size");
   f32x4 acc[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
   constexpr int KPL = DH / 4;  // k per lane group
 #pragma unroll
   for (int j4 = 0; j4 < KPL / 4; ++j4) {
     const f32x4 qv = *reinterpret_cast<const f32x4*>(qrow + lq * KPL + 4 * j4);
-    f32x4 kv = *reinterpret_cast<const f32x4*>(krow + lq * KPL + 4 * j4);
-    if (!kvalid) kv = f32x4{0.f, 0.f, 0.f, 0.f};
+    const f32x4 kv = *reinterpret_cast<const f32x4*>(krow + lq * KPL + 4 * j4);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] = mfma4(qv[e], kv[e], acc[e]);
+    for (int e = 0; e < 4; ++e) acc[e] = mfma4(kv[e], qv[e], acc[e]);
   }
-  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  return (acc[0] + acc[2]) + (acc[1] + acc[3]);
 }
 
 // waves sharing one (head, 16-query block) of attention: each repeats the
@@ -99,35 +104,39 @@ constexpr int attn_waves_per_pair(int nw, int npair, int ncb) {
   return wpp;
 }
 
-// Cross-lane moves within a row of 16 lanes (DPP): swap neighbours, swap
-// pairs, mirror within 8, mirror within 16.  Each pairs every lane with a
-// lane of the other half of its group, so four steps combine all 16 lanes
-// and every lane ends with the same value.
+// Cross-lane moves within a quad of lanes (DPP): swap neighbours (0xB1),
+// swap pairs (0x4E).
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
-__device__ __forceinline__ float row16_sum(float v) {
-  v += dpp_mov<0xB1>(v);
-  v += dpp_mov<0x4E>(v);
-  v += dpp_mov<0x141>(v);
-  v += dpp_mov<0x140>(v);
-  return v;
-}
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, dpp_mov<0xB1>(v));
-  v = fmaxf(v, dpp_mov<0x4E>(v));
-  v = fmaxf(v, dpp_mov<0x141>(v));
-  v = fmaxf(v, dpp_mov<0x140>(v));
-  return v;
-}
 
-// Orders a wave's own LDS writes before its following LDS reads (other
-// lanes' data) without a workgroup barrier.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// The values of the two lanes 16 (32) apart that share a lane's low bits, in
+// lane order and the same in both lanes: a symmetric function of the pair
+// gives both the same bits.  A 16x16 accumulator holds a row in the four
+// lanes l, l + 16, l + 32, l + 48, so two such steps reduce a row.
+struct Pair {
+  float a, b;
+};
+__device__ __forceinline__ Pair swap16(float v) {
+  const u32x2 r = __builtin_bit_cast(
+      u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ Pair swap32(float v) {
+  const u32x2 r = __builtin_bit_cast(
+      u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ float quad_rows_sum(float v) {
+  Pair p = swap16(v);
+  p = swap32(p.a + p.b);
+  return p.a + p.b;
+}
+__device__ __forceinline__ float quad_rows_max(float v) {
+  Pair p = swap16(v);
+  p = swap32(fmaxf(p.a, p.b));
+  return fmaxf(p.a, p.b);
 }
 
 // Operand traits of the two matmul precisions.  A fragment is 16 bytes per
@@ -140,25 +149,30 @@ template <> struct Op<__bf16> {
   __device__ static __forceinline__ void store(__bf16* buf, int ld, int row, int k, float v) {
     reinterpret_cast<uint16_t*>(buf)[row * ld + k] = (uint16_t)bf16_rne(v);
   }
-  __device__ static __forceinline__ void mma(f32x4& acc, uint4 a, uint4 b) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
-                                                  __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
+  // four consecutive k (k a multiple of 4)
+  __device__ static __forceinline__ void store4(__bf16* buf, int ld, int row, int k, f32x4 v) {
+    *reinterpret_cast<u32x2*>(buf + row * ld + k) = u32x2{bf16x2_rne(v[0], v[1]), bf16x2_rne(v[2], v[3])};
+  }
+  // acc (rows: output columns, columns: tile rows) += weights w x activations a
+  __device__ static __forceinline__ void mma(f32x4& acc, uint4 w, uint4 a) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w),
+                                                  __builtin_bit_cast(bf16x8_t, a), acc, 0, 0, 0);
   }
 };
 
 template <> struct Op<float> {
+  // a lane's four consecutive k feed four 16x16x4 MFMAs (k order permuted
+  // alike in both operands)
   static constexpr int KF = 16, VE = 4, PAD = 4;
-  // Within each 16-wide k block, element k is stored at 4*(k%4) + (k/4)%4 so
-  // that the four values one lane feeds to four 16x16x4 MFMAs are adjacent.
-  __device__ static __forceinline__ int pcol(int k) { return (k & ~15) | ((k & 3) << 2) | ((k >> 2) & 3); }
-  __device__ static __forceinline__ void store(float* buf, int ld, int row, int k, float v) {
-    buf[row * ld + pcol(k)] = v;
+  __device__ static __forceinline__ void store(float* buf, int ld, int row, int k, float v) { buf[row * ld + k] = v; }
+  __device__ static __forceinline__ void store4(float* buf, int ld, int row, int k, f32x4 v) {
+    *reinterpret_cast<f32x4*>(buf + row * ld + k) = v;
   }
-  __device__ static __forceinline__ void mma(f32x4& acc, uint4 a, uint4 b) {
-    acc = mfma4(__uint_as_float(a.x), __uint_as_float(b.x), acc);
-    acc = mfma4(__uint_as_float(a.y), __uint_as_float(b.y), acc);
-    acc = mfma4(__uint_as_float(a.z), __uint_as_float(b.z), acc);
-    acc = mfma4(__uint_as_float(a.w), __uint_as_float(b.w), acc);
+  __device__ static __forceinline__ void mma(f32x4& acc, uint4 w, uint4 a) {
+    acc = mfma4(__uint_as_float(w.x), __uint_as_float(a.x), acc);
+    acc = mfma4(__uint_as_float(w.y), __uint_as_float(a.y), acc);
+    acc = mfma4(__uint_as_float(w.z), __uint_as_float(a.z), acc);
+    acc = mfma4(__uint_as_float(w.w), __uint_as_float(a.w), acc);
   }
 };
 
@@ -187,7 +201,7 @@ __device__ __forceinline__ void gemm_pref(uint4 (&bc)[NP][MPW], const uint4* W, 
     for (int m = 0; m < MPW; ++m) bc[d][m] = W[((size_t)gcb(m) * KBT + kf0 + d) * 64 + lane];
 }
 
-// acc[m][rb] += A[rb*16 .. +16][k-range] x W[col block gcb(m)][k-range]^T
+// acc[m][rb] += (A[rb*16 .. +16][k-range] x W[col block gcb(m)][k-range]^T)^T
 // A: LDS operand, row stride lda elements, offset to the k-range start.
 // W: packed fragments of a matrix with KBT fragments per column block; kf0
 // is the first fragment of the k-range, NKF its length; bc holds the
@@ -228,7 +242,7 @@ __device__ __forceinline__ void gemm_run(f32x4 (&acc)[MPW][RBk], const AT* A, in
 #pragma unroll
     for (int m = 0; m < MPW; ++m)
 #pragma unroll
-      for (int rb = 0; rb < RBk; ++rb) O::mma(acc[m][rb], a[rb], buf[kf % (PD + 1)][m]);
+      for (int rb = 0; rb < RBk; ++rb) O::mma(acc[m][rb], buf[kf % (PD + 1)][m], a[rb]);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -239,6 +253,12 @@ __device__ __forceinline__ void gemm_acc(f32x4 (&acc)[MPW][RBk], const AT* A, in
   uint4 bc[1][MPW];
   gemm_pref<1, MPW>(bc, W, KBT, kf0, gcb, lane);
   gemm_run<AT, RBk, MPW, NKF, 6, 1>(acc, A, lda, W, KBT, kf0, gcb, lane, bc);
+}
+
+// a value every lane of the wave holds alike, as a scalar
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return (uint64_t)hi << 32 | lo;
 }
 
 // Hardware transcendental approximations (v_rsq_f32, v_exp_f32, v_rcp_f32;
@@ -264,7 +284,7 @@ __device__ __forceinline__ float gelu_erf(float v) {
   return 0.5f * v * (v >= 0.f ? 2.0f - q : q);
 }
 
-template <int D, int DH, int HZ, int SPT, int DFF, int NW, int HG, int FC, int SMAX, int TEAM>
+template <class AT, int D, int DH, int HZ, int SPT, int DFF, int NW, int HG, int FC, int SMAX, int TEAM>
 struct Cfg {
   static constexpr int NWV = NW;
   static constexpr int NT = NW * 64;
@@ -280,14 +300,72 @@ struct Cfg {
   static constexpr int NJB = HZ >= 16 ? HZ / 16 : 1;   // key blocks per query block (self-attention)
   static constexpr int SPB = HZ >= 16 ? 1 : 16 / HZ;   // samples per 16-row block
   static constexpr int SLOTS = 16 / SPB;               // memory columns per sample in a 16-wide tile
-  static constexpr int PS = 17;                        // stride of a 16x16 fp32 scratch tile
-  static constexpr int PWN = (NJB > RB ? NJB : RB) * 16 * PS;
+  static constexpr int LDR = 2 * NW + 4;               // LayerNorm partials per row (padded: no bank conflicts)
   static constexpr int NB = (8 / (CBW * RB)) > 0 ? (8 / (CBW * RB)) : 1;  // reuse loads per batch
   // cross-attention folded into per-token fold records (width 256; one
   // sample per 16-row block); used when n_heads x memory tokens <= 16
   static constexpr bool FOLD = D == 256 && HZ >= 16;
   static constexpr int REC = 2 * NH * D + 16;                              // floats per fold record
-  static constexpr int FOLD_LDS = FOLD ? NW * RB * 256 + 16 * R + RB * 16 * D : 0;
+  static constexpr int FOLD_LDS = FOLD ? NW * RB * 256 : 0;  // partial scores of the waves
+
+  // Weight streams.  A wave's fragments of one group of a unit (TY 0
+  // self-attention: a head group's q, k, v columns, then its slice of W_o;
+  // 1 projected cross-attention: q columns, W_o2; 2 feed-forward: a chunk of
+  // W_1, then of W_2) form one sequence, in the order they are multiplied,
+  // and travel through a ring of P fragments of registers: the first P are
+  // requested before the unit's LayerNorm, the load of sequence element i + P
+  // is issued when element i has been multiplied, and the last P loads of a
+  // group are the first P of the unit's next one, so a wave has P KiB of
+  // weights in flight from the unit's start to its end, also while attention
+  // and GELU run.
+  static constexpr int KF = sizeof(AT) == 2 ? 32 : 16;
+  static constexpr int K1 = D / KF;  // k-steps of a product over d
+  static constexpr int m1(int ty) { return (ty == 0 ? 3 * GW / 16 : ty == 1 ? GW / 16 : FC / 16) / NW; }
+  // column blocks multiplied together in stage 1 (feed-forward with bf16
+  // operands: two at a time, so that the GELU of one pair runs while the next
+  // pair streams; fp32 products need the independent accumulators of more)
+  static constexpr int g1(int ty) { return ty == 2 && sizeof(AT) == 2 && m1(2) % 2 == 0 ? 2 : m1(ty); }
+  static constexpr int k2(int ty) { return (ty == 2 ? FC : GW) / KF; }
+  static constexpr int kbt2(int ty) { return ty == 2 ? DFF / KF : K1; }  // fragments per column block, stage 2
+  static constexpr int s1(int ty) { return K1 * m1(ty); }
+  static constexpr int total(int ty) { return s1(ty) + k2(ty) * CBW; }
+  // ring size: 16 fragments a wave, or what divides a short sequence (8
+  // waves: 128 KiB in flight per CU; Push-T batch 1 with bf16 operands 3.54,
+  // 3.42, 3.35, 3.35 ms with 4, 8, 16, 32; width 768 at batch 128 38.8, 37.2,
+  // 37.1, 55.7 ms: more spills)
+  static constexpr int PLIM = 16;
+  static constexpr int ring_size() {
+    int p = PLIM;
+    while (p > 1 && (total(0) < p || total(1) < p || total(2) < p || total(0) % p || total(2) % p)) p /= 2;
+    return p;
+  }
+  // float offsets of one layer's small tensors (flat order of evo.h) from the
+  // layer's first parameter, and a layer's parameter count
+  static constexpr int DD = D * D;
+  static constexpr int pLN1 = 0, pBQKV = 2 * D + 3 * DD, pBO = 5 * D + 4 * DD, pLN2 = 6 * D + 4 * DD,
+                       pBQ = 8 * D + 5 * DD, pBO2 = 11 * D + 8 * DD, pLN3 = 12 * D + 8 * DD,
+                       pB1 = 14 * D + 8 * DD + DFF * D, pB2 = 14 * D + 8 * DD + DFF + 2 * DFF * D,
+                       PLAYER = 15 * D + 8 * DD + DFF + 2 * DFF * D;
+  // sequence length with the padding that keeps the next sequence at slot 0
+  static constexpr int padded(int ty) { return (total(ty) + ring_size() - 1) / ring_size() * ring_size(); }
+  // byte offsets inside one layer's packed matrices (qkv, o, q, kv, o2, w1, w2)
+  static constexpr int FB = D * D / (16 * KF) * 1024;  // a d x d matrix
+  static constexpr int LAYER = 8 * FB + 2 * (DFF / D) * FB;
+  static constexpr int off1(int ty) { return ty == 0 ? 0 : ty == 1 ? 4 * FB : 8 * FB; }
+  static constexpr int off2(int ty) { return ty == 0 ? 3 * FB : ty == 1 ? 7 * FB : 8 * FB + (DFF / D) * FB; }
+  // constant part of the offset of sequence element i
+  static constexpr int elem(int ty, int i) {
+    if (i < s1(ty)) {
+      const int r = i % (K1 * g1(ty)), k = r / g1(ty), m = i / (K1 * g1(ty)) * g1(ty) + r % g1(ty);
+      const int nb = ty == 0 ? (NW * m) / (GW / 16) * CB + (NW * m) % (GW / 16) : NW * m;
+      return off1(ty) + (nb * K1 + k) * 1024;
+    }
+    const int j = i - s1(ty);
+    return off2(ty) + (j % CBW * kbt2(ty) + j / CBW) * 1024;
+  }
+  // wave- and group-dependent part (layer base included by the caller)
+  static constexpr int wave1(int ty, int w, int g) { return (g * ((ty == 2 ? FC : GW) / 16) + w) * K1 * 1024; }
+  static constexpr int wave2(int ty, int w, int g) { return (w * CBW * kbt2(ty) + g * k2(ty)) * 1024; }
 };
 
 // Cross-attention with few memory tokens, folded.  With q = x W_q^T + b_q
@@ -299,8 +377,7 @@ struct Cfg {
 // S tokens once per (token, layer) replaces the two d x d products of every
 // evaluation by two products with S x n_heads columns.
 //
-// A fold record holds u [NH][D] (for fp32 operands in the fragment column
-// order of the LDS operand, Op<float>::pcol), w [NH][D] and c [NH].  The
+// A fold record holds u [NH][D], w [NH][D] and c [NH].  The
 // workgroup folds `nrows` <= MR key/value rows (kv: [row][2D] keys then
 // values, row stride ldkv, in LDS) with the layer's W_q (rows), the
 // transposed W_o2 (row e = column e of W_o2) and b_q; dst(row) is the record
@@ -348,15 +425,7 @@ __device__ void fold_rows(const float* __restrict__ raw, uint32_t wq, uint32_t w
       if (r < nrows) {
         float* q = dst(r);
         if (!q) continue;
-        if (isw) {
-          *reinterpret_cast<f32x4*>(q + NH * D + hd * D + c0) = acc[r];
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const int c = c0 + t;
-            q[hd * D + (BF ? c : ((c & ~15) | ((c & 3) << 2) | ((c >> 2) & 3)))] = acc[r][t];
-          }
-        }
+        *reinterpret_cast<f32x4*>(q + (isw ? NH * D : 0) + hd * D + c0) = acc[r];
       }
   }
   for (int it = tid; it < nrows * NH; it += NT) {
@@ -368,81 +437,65 @@ __device__ void fold_rows(const float* __restrict__ raw, uint32_t wq, uint32_t w
   }
 }
 
-// LayerNorm statistics of the tile rows from the register-resident stream:
-// per-lane (mean, M2) over its columns, merged across the 16 lanes of a row
-// group with shuffles; the waves' partials meet in LDS (one barrier) and
-// every wave merges them for all rows in a fixed tree (pairwise, equal
-// counts), so all waves hold the same bits.
+// LayerNorm statistics of the tile rows from the register-resident stream: a
+// lane takes (mean, M2) of its columns of its row, two lane swaps merge the
+// four lanes of the row, the waves' partials meet in LDS (one barrier), and
+// every lane merges its row's partials itself in a fixed tree (pairwise,
+// equal counts), so all waves hold the same bits.
+// (m, q) of two equal groups of n values each: mean of the two means, M2 sum
+// plus the spread term (symmetric, so both partners agree bitwise)
+__device__ __forceinline__ void merge_stats(float& m, float& q, float ma, float qa, float mb, float qb, float n) {
+  const float d = mb - ma;
+  m = 0.5f * (ma + mb);
+  q = qa + qb + d * d * (0.5f * n);
+}
 template <class C>
-__device__ __forceinline__ void ln_stats(const f32x4 (&h)[C::CBW][C::RB], float (*red)[C::R][2],
-                                         float (&mu)[C::RB][4], float (&rs)[C::RB][4], int w, int lc, int lq) {
-  constexpr int D = C::CB * 16;
-  constexpr float nw = 16.0f * C::CBW;
+__device__ __forceinline__ void ln_stats(const f32x4 (&h)[C::CBW][C::RB], float (*red)[C::LDR], float (&mu)[C::RB],
+                                         float (&rs)[C::RB], int w, int lc, int lq) {
+  constexpr int D = C::CB * 16, NWV = C::NWV;
+  static_assert((NWV & (NWV - 1)) == 0, "pairwise merges of the waves");
 #pragma unroll
-  for (int rb = 0; rb < C::RB; ++rb)
+  for (int rb = 0; rb < C::RB; ++rb) {
+    float m = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float m = 0.f;
+    for (int c = 0; c < C::CBW; ++c) m += (h[c][rb][0] + h[c][rb][1]) + (h[c][rb][2] + h[c][rb][3]);
+    m *= 0.25f / C::CBW;
+    float q = 0.f;
 #pragma unroll
-      for (int c = 0; c < C::CBW; ++c) m += h[c][rb][i];
-      m *= (1.0f / C::CBW);
-      float q = 0.f;
+    for (int c = 0; c < C::CBW; ++c)
 #pragma unroll
-      for (int c = 0; c < C::CBW; ++c) {
+      for (int i = 0; i < 4; ++i) {
         const float e = h[c][rb][i] - m;
         q += e * e;
       }
-      // merge equal-count groups pairwise: mean of the two means, M2 sum
-      // plus the spread term (symmetric, so both partners agree bitwise)
-      float n = (float)C::CBW;
-      const auto merge = [&](float mo, float qo) {
-        const float d = mo - m;
-        m = 0.5f * (m + mo);
-        q = q + qo + d * d * (0.5f * n);
-        n *= 2.f;
-      };
-      merge(dpp_mov<0xB1>(m), dpp_mov<0xB1>(q));
-      merge(dpp_mov<0x4E>(m), dpp_mov<0x4E>(q));
-      merge(dpp_mov<0x141>(m), dpp_mov<0x141>(q));
-      merge(dpp_mov<0x140>(m), dpp_mov<0x140>(q));
-      if (lc == 0) {
-        red[w][rb * 16 + lq * 4 + i][0] = m;
-        red[w][rb * 16 + lq * 4 + i][1] = q;
-      }
-    }
+    Pair pm = swap16(m), pq = swap16(q);
+    merge_stats(m, q, pm.a, pq.a, pm.b, pq.b, 4.f * C::CBW);
+    pm = swap32(m);
+    pq = swap32(q);
+    merge_stats(m, q, pm.a, pq.a, pm.b, pq.b, 8.f * C::CBW);
+    if (lq == 0) *reinterpret_cast<f32x2*>(&red[rb * 16 + lc][2 * w]) = f32x2{m, q};
+  }
   __syncthreads();
-  // every wave merges the wave partials itself (no second barrier): the
-  // four lanes of a quad take one row, each its share of the waves, then
-  // two symmetric quad merges give all four the same bits; lane l then
-  // holds the statistics of row l / 4 of the row block
-  static_assert(C::NWV % 4 == 0, "waves per quad lane");
-  constexpr int WPL = C::NWV / 4;
-  const int lane = lc + 16 * lq, qrow = lane >> 2, qp = lane & 3;
 #pragma unroll
   for (int rb = 0; rb < C::RB; ++rb) {
-    const int row = rb * 16 + qrow;
-    float m = red[qp * WPL][row][0], q = red[qp * WPL][row][1], n = nw;
-    const auto merge = [&](float mo, float qo) {
-      const float d = mo - m;
-      m = 0.5f * (m + mo);
-      q = q + qo + d * d * (0.5f * n);
-      n *= 2.f;
-    };
+    float m[NWV], q[NWV];
 #pragma unroll
-    for (int x = 1; x < WPL; ++x) merge(red[qp * WPL + x][row][0], red[qp * WPL + x][row][1]);
-    merge(dpp_mov<0xB1>(m), dpp_mov<0xB1>(q));
-    merge(dpp_mov<0x4E>(m), dpp_mov<0x4E>(q));
-    const float r_ = fast_rsqrt(q * (1.0f / D) + 1e-5f);
-    // rows lq * 4 + i sit in lanes 16 lq + 4 i: a swizzle inside each
-    // 32-lane half keeps lane bit 4 and sets bits 2..3 to i
-#define EVO_LN_PICK(i)                                                                              \
-    mu[rb][i] = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(m), 0x10 | ((4 * (i)) << 5))); \
-    rs[rb][i] = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(r_), 0x10 | ((4 * (i)) << 5)));
-    EVO_LN_PICK(0)
-    EVO_LN_PICK(1)
-    EVO_LN_PICK(2)
-    EVO_LN_PICK(3)
-#undef EVO_LN_PICK
+    for (int x = 0; x < NWV / 2; ++x) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&red[rb * 16 + lc][4 * x]);
+      m[2 * x] = v[0];
+      q[2 * x] = v[1];
+      m[2 * x + 1] = v[2];
+      q[2 * x + 1] = v[3];
+    }
+    float n = 16.f * C::CBW;
+#pragma unroll
+    for (int st = 1; st < NWV; st *= 2) {
+#pragma unroll
+      for (int x = 0; x < NWV; x += 2 * st) merge_stats(m[x], q[x], m[x], q[x], m[x + st], q[x + st], n);
+      n *= 2.f;
+    }
+    mu[rb] = m[0];
+    rs[rb] = fast_rsqrt(q[0] * (1.0f / D) + 1e-5f);
   }
 }
 
@@ -450,16 +503,16 @@ template <class AT, int D, int DH, int HZ, int SPT, int DFF, int NW, int HG, int
 __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   using O = Op<AT>;
   using OF = Op<float>;
-  using C = Cfg<D, DH, HZ, SPT, DFF, NW, HG, FC, SMAX, TEAM>;
+  using C = Cfg<AT, D, DH, HZ, SPT, DFF, NW, HG, FC, SMAX, TEAM>;
   constexpr int NT = C::NT, R = C::R, RB = C::RB, NH = C::NH, CB = C::CB, CBW = C::CBW, GW = C::GW;
   constexpr int LDA = D + O::PAD, LDY = C::LDY, LDZ = C::ZW + O::PAD;
   constexpr int KOBS = C::KOBS, LDO = KOBS + O::PAD;
-  constexpr int NJB = C::NJB, SLOTS = C::SLOTS, PS = C::PS, PWN = C::PWN, NB = C::NB;
+  constexpr int NJB = C::NJB, SLOTS = C::SLOTS, NB = C::NB;
   static_assert(R % 16 == 0 && CB % NW == 0 && NH % HG == 0 && DFF % FC == 0, "tile shape");
   static_assert((3 * GW / 16) % NW == 0 && (GW / 16) % NW == 0 && (FC / 16) % NW == 0, "block split");
   static_assert((NH / HG) % TEAM == 0 && (DFF / FC) % TEAM == 0, "team members split head groups and chunks");
   static_assert(HZ % 4 == 0 && (HZ & (HZ - 1)) == 0 && HZ <= 64, "horizon must be a power of two in [4, 64]");
-  static_assert(NW * R * 16 <= R * LDY, "head partials must fit the stage-1 buffer");
+  static_assert(NW * RB * 256 <= R * LDY, "head partials must fit the stage-1 buffer");
   static_assert(16 * LDO * (int)sizeof(AT) <= R * LDY * 4, "observation operand must fit");
   static_assert(SMAX <= SLOTS, "memory tokens per sample must fit a 16-column tile");
   static_assert(DH % 16 == 0, "head dim");
@@ -471,13 +524,6 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   // layer-merged residual sum accumulated in registers, else in its cache slot
   constexpr bool MAC_REG = CBW * RB <= 4;
   static_assert(MAC_REG || SPT == 1 || sizeof(AT) == 4, "bf16 layer sums in memory need one sample per tile");
-  // weight fragments in flight per wave in the unit products (at width 768
-  // and in two-sample bf16 tiles the residual stream and the unit output
-  // leave room for 8)
-  constexpr int INFL = D > 256 ? 8
-                       : (TEAM > 1 && RB == 1) ? 16
-                       : (RB == 1 && CBW <= 2) ? 12
-                       : sizeof(AT) == 2 ? 8 : 6;
   constexpr float kScale = (DH == 64) ? 0.125f : (DH == 32 ? 0.17677669529663688f : 0.0f);
   static_assert(DH == 64 || DH == 32, "head dim");
 
@@ -486,18 +532,17 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   // the feed-forward chunks alternate between two operand buffers, so a
   // chunk's GELU outputs never overwrite the previous chunk's while a wave
   // may still read them, and no barrier ends a chunk (where LDS allows)
-  constexpr bool ZB2 = D <= 256 && !(sizeof(AT) == 4 && SPT > 1);
+  constexpr bool ZB2 = DFF / FC > TEAM && !(sizeof(AT) == 4 && SPT > 1) && R * LDZ * (int)sizeof(AT) <= 20 * 1024;
   __shared__ __attribute__((aligned(16))) AT zbuf[(ZB2 ? 2 : 1) * R * LDZ];
-  __shared__ __attribute__((aligned(16))) float pw[NW * PWN];
   __shared__ __attribute__((aligned(16))) float kvbuf[SPT * SMAX * 2 * GW];
-  __shared__ float red[NW][R][2];
-  __shared__ __attribute__((aligned(16))) float xs[R * 16];
+  __shared__ __attribute__((aligned(16))) float red[R][C::LDR];
   __shared__ uint64_t msk[kMaskEntries * 3];
-  __shared__ LayerOff s_loff[kMaxLayers];
-  __shared__ PackOff s_poff[kMaxLayers];
   __shared__ int smp[SPT];
 
-  const int tid = threadIdx.x, w = tid >> 6;
+  const int tid = threadIdx.x;
+  // the wave index in a scalar register: weight, bias and cache addresses
+  // are then scalar bases plus one per-lane offset
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   // lane indices are made opaque to the optimiser (an empty asm) once per
   // step, unit, head group and d_ff chunk, so that the address arithmetic
   // derived from them is recomputed inside the loops instead of being
@@ -519,20 +564,32 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   if (tid < SPT) smp[tid] = p.tile_sample[tile * SPT + tid];
   if (tid == 0) s_abort = 0;
   float* const okv = p.okv + (size_t)member * p.okv_member_stride;
-  for (int it = tid; it < L * (int)(sizeof(LayerOff) / 4); it += NT)
-    reinterpret_cast<uint32_t*>(s_loff)[it] = reinterpret_cast<const uint32_t*>(p.loff)[it];
-  for (int it = tid; it < L * (int)(sizeof(PackOff) / 8); it += NT)
-    reinterpret_cast<uint64_t*>(s_poff)[it] = reinterpret_cast<const uint64_t*>(p.poff)[it];
   for (int it = tid; it < SPT * T * 3; it += NT) {
     const int j = it / (T * 3), r = it % (T * 3);
     msk[it] = p.masks[(size_t)p.tile_slot[tile * SPT + j] * T * 3 + r];
   }
   __syncthreads();
 
-  // initial sample x_T, stored [row][pcol(a)] (zero-padded to 16 columns)
-  for (int it = tid; it < R * 16; it += NT) {
-    const int row = it / 16, a = it % 16, s = smp[row / HZ];
-    xs[row * 16 + OF::pcol(a)] = (s >= 0 && a < A) ? p.noise[((size_t)s * HZ + (row % HZ)) * A + a] : 0.f;
+  // the tile's samples as scalars, and the sample of this lane's rows in
+  // row block rb
+  int ssmp[SPT];
+#pragma unroll
+  for (int j = 0; j < SPT; ++j) ssmp[j] = __builtin_amdgcn_readfirstlane(smp[j]);
+  const auto row_sample = [&](int rb) { return HZ >= 16 ? ssmp[rb * 16 / HZ] : smp[(rb * 16 + lc) / HZ]; };
+
+  // current sample x_t of this lane's rows (row rb * 16 + lc, actions
+  // 4 lq .. + 3, zero beyond A): every wave keeps its own copy and updates it
+  // alike, so that the sampler's result feeds the next step's embedding
+  // product from registers
+  f32x4 xv[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = rb * 16 + lc, s = row_sample(rb);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int a = 4 * lq + i;
+      xv[rb][i] = (s >= 0 && a < A) ? p.noise[((size_t)s * HZ + (row % HZ)) * A + a] : 0.f;
+    }
   }
 
   // ---- per query: observation tokens and their keys/values in every layer
@@ -560,19 +617,16 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
                                            [&](int m) { return w + NW * m; }, lane);
     }
     // memory-token operand rows (row = slot*n_obs + token) in xa
+    const int orow = lc, oj = orow / nobs, oo = orow % nobs;
+    const bool olive = orow < SPT * nobs && smp[oj] >= 0;
 #pragma unroll
     for (int m = 0; m < MPWO; ++m) {
-      const int gcol = (w + NW * m) * 16 + lc;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = lq * 4 + i;
-        float v = 0.f;
-        if (row < SPT * nobs) {
-          const int j = row / nobs, o = row % nobs;
-          if (smp[j] >= 0) v = acc[m][0][i] + raw[p.b_obs + gcol] + raw[p.P_mem + (size_t)(1 + o) * D + gcol];
-        }
-        O::store(xa, LDA, row, gcol, v);
-      }
+      const int gcol = (w + NW * m) * 16 + lq * 4;
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (olive)
+        v = acc[m][0] + *reinterpret_cast<const f32x4*>(raw + p.b_obs + gcol) +
+            *reinterpret_cast<const f32x4*>(raw + p.P_mem + (size_t)(1 + oo) * D + gcol);
+      O::store4(xa, LDA, orow, gcol, v);
     }
     __syncthreads();
     constexpr int MPWK = 2 * CB / NW;
@@ -580,30 +634,24 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
       f32x4 kv[MPWK][1];
 #pragma unroll
       for (int m = 0; m < MPWK; ++m) kv[m][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-      gemm_acc<AT, 1, MPWK, D / O::KF>(kv, xa, LDA, p.pk + s_poff[l].kv, D / O::KF, 0,
+      gemm_acc<AT, 1, MPWK, D / O::KF>(kv, xa, LDA, p.pk + p.poff[l].kv, D / O::KF, 0,
                                         [&](int m) { return w + NW * m; }, lane);
-      const uint32_t bkv = s_loff[l].b_kv;
+      const uint32_t bkv = p.loff[l].b_kv;
 #pragma unroll
       for (int m = 0; m < MPWK; ++m) {
-        const int gcol = (w + NW * m) * 16 + lc;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = lq * 4 + i;
-          if (row < SPT * nobs) {
-            const int j = row / nobs, o = row % nobs;
-            if (smp[j] >= 0)
-              okv[(((size_t)smp[j] * L + l) * nobs + o) * (2 * D) + gcol] = kv[m][0][i] + raw[bkv + gcol];
-          }
-        }
+        const int gcol = (w + NW * m) * 16 + lq * 4;
+        if (olive)
+          *reinterpret_cast<f32x4*>(okv + (((size_t)smp[oj] * L + l) * nobs + oo) * (2 * D) + gcol) =
+              kv[m][0] + *reinterpret_cast<const f32x4*>(raw + bkv + gcol);
       }
     }
     __syncthreads();
   }
 
-  // sample slot of each of this lane's fragment row groups (4 rows, one sample)
+  // sample slot of each of this lane's rows
   int jrow[RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) jrow[rb] = (rb * 16 + lq * 4) / HZ;
+  for (int rb = 0; rb < RB; ++rb) jrow[rb] = HZ >= 16 ? rb * 16 / HZ : (rb * 16 + lc) / HZ;
   // residual caches of this workgroup: [3L][R*D] values in fragment order.
   // fp16 with bf16 operands (rounded once per stored residual, clamped to
   // the finite fp16 range; the stream and the layer sums stay fp32): half
@@ -700,30 +748,34 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   // later reads only its own LDS entries, so no barrier is needed)
   __shared__ uint4 s_win[EMB_LDS ? CB * 64 : 1], s_wout[EMB_LDS ? CB * 64 : 1];
   __shared__ f32x4 s_pb[PB_LDS ? CB * 64 : 1];
-  __shared__ float s_lf[EMB_LDS ? 2 * D : 1];
+  __shared__ __attribute__((aligned(16))) float s_lf[EMB_LDS ? 2 * D : 4];
   constexpr int KE = KEEP_EMB ? CBW : 1, KP = (KEEP_EMB || (EMB_LDS && !PB_LDS)) ? CBW : 1;
   uint4 win[KE], wout[KE];
   f32x4 pb[KP][KP > 1 ? RB : 1];
-  float lfg[KE], lfb[KE];
+  f32x4 lfg[KE], lfb[KE];
+  // b_in + P_act of this lane's row and columns
+  const auto row_bias = [&](int c, int rb) {
+    const int col = (w * CBW + c) * 16 + lq * 4;
+    return *reinterpret_cast<const f32x4*>(raw + p.b_in + col) +
+           *reinterpret_cast<const f32x4*>(raw + p.P_act + (size_t)((rb * 16 + lc) % HZ) * D + col);
+  };
   if constexpr (KEEP_EMB || EMB_LDS) {
 #pragma unroll
     for (int c = 0; c < CBW; ++c) {
-      const int col = (w * CBW + c) * 16 + lc, fi = (w * CBW + c) * 64 + lane;
+      const int col = (w * CBW + c) * 16 + lq * 4, fi = (w * CBW + c) * 64 + lane;
       const uint4 wi = pk[p.pk_win + (size_t)fi], wo = pk[p.pk_wout + (size_t)fi];
-      const float bi = raw[p.b_in + col];
       f32x4 pv[RB];
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pv[rb][i] = bi + raw[p.P_act + (size_t)((rb * 16 + lq * 4 + i) % HZ) * D + col];
-      const float g_ = raw[p.lnf_g + col], b_ = raw[p.lnf_b + col];
+      for (int rb = 0; rb < RB; ++rb) pv[rb] = row_bias(c, rb);
+      const f32x4 g_ = *reinterpret_cast<const f32x4*>(raw + p.lnf_g + col);
+      const f32x4 b_ = *reinterpret_cast<const f32x4*>(raw + p.lnf_b + col);
       if constexpr (EMB_LDS) {
         s_win[fi] = wi;
         s_wout[fi] = wo;
         if constexpr (PB_LDS) s_pb[fi] = pv[0];
         else pb[c][0] = pv[0];
-        s_lf[col] = g_;
-        s_lf[D + col] = b_;
+        *reinterpret_cast<f32x4*>(s_lf + col) = g_;
+        *reinterpret_cast<f32x4*>(s_lf + D + col) = b_;
       } else {
         win[c] = wi;
         wout[c] = wo;
@@ -734,6 +786,10 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
       }
     }
   }
+  // head bias of this lane's actions (zero beyond A)
+  f32x4 bout;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) bout[i] = 4 * lq + i < A ? raw[p.b_out + 4 * lq + i] : 0.f;
 
   f32x4 h[CBW][RB], mac[MAC_REG ? CBW : 1][MAC_REG ? RB : 1];
 #pragma unroll
@@ -742,39 +798,31 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
     for (int rb = 0; rb < (MAC_REG ? RB : 1); ++rb) mac[c][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // LayerNorm gain/shift and output bias of the next unit to evaluate, for
-  // this lane's columns (loaded one unit ahead)
-  float nlg[CBW], nlb[CBW], nrb[CBW];
-  // Width 256: every prefetch below is issued unconditionally (a merge of
-  // an in-flight load with an older register value costs a wait for the
-  // load at the merge).  Width 768 keeps the conditional form, which its
-  // register allocation favours.
-  constexpr bool UNCOND = D <= 256;
-  int loaded_t = -1, loaded_u = -1;  // (step, unit) the prefetched parameters belong to
-  const auto load_unit_params = [&](int tt, int unit) {
-    loaded_t = tt;
-    loaded_u = unit;
-    const int ul = unit / 3, uu = unit - 3 * ul;
-    const LayerOff& q = s_loff[ul];
-    const uint32_t go = uu == 0 ? q.ln1_g : (uu == 1 ? q.ln2_g : q.ln3_g);
-    const uint32_t bo = uu == 0 ? q.ln1_b : (uu == 1 ? q.ln2_b : q.ln3_b);
-    const uint32_t ro = uu == 0 ? q.b_o : (uu == 1 ? q.b_o2 : q.b_2);
+  // this lane's columns.  Width 256: loaded one unit ahead, and every
+  // prefetch is issued unconditionally (a merge of an in-flight load with an
+  // older register value costs a wait for the load at the merge).  Width 768
+  // has no registers for that: gain and shift are requested with the unit's
+  // first weights, the bias before the residual is summed.
+  constexpr bool AHEAD = D <= 256;
+  f32x4 nlg[CBW], nlb[CBW], nrb[AHEAD ? CBW : 1];
+  // four consecutive small parameters of the layers, at float offset off (a
+  // scalar) from layer 0 plus the lane group's four columns
+  const auto prs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(raw + p.raw_layers), (short)0, L * C::PLAYER * 4,
+                                                     0x00020000);
+  const auto lparam = [&](int off) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(prs, lq * 16, off * 4, 0));
+  };
+  const auto load_unit_params = [&](int unit) {
+    const int ul = unit / 3, uu = unit - 3 * ul, base = ul * C::PLAYER + w * CBW * 16;
+    const int go = base + (uu == 0 ? C::pLN1 : (uu == 1 ? C::pLN2 : C::pLN3));
+    const int ro = base + (uu == 0 ? C::pBO : (uu == 1 ? C::pBO2 : C::pB2));
 #pragma unroll
     for (int c = 0; c < CBW; ++c) {
-      const int col = (w * CBW + c) * 16 + lc;
-      nlg[c] = raw[go + col];
-      nlb[c] = raw[bo + col];
-      nrb[c] = raw[ro + col];
+      nlg[c] = lparam(go + c * 16);
+      nlb[c] = lparam(go + D + c * 16);
+      if constexpr (AHEAD) nrb[c] = lparam(ro + c * 16);
     }
   };
-  // first unit any sample of the tile evaluates at step tt (U if none)
-  const auto first_eval = [&](int tt) {
-    uint64_t m = 0;
-#pragma unroll
-    for (int j = 0; j < SPT; ++j)
-      if (smp[j] >= 0) m |= msk[(j * T + tt) * 3 + 0] & ~kMergedBit;
-    return m ? __builtin_ctzll(m) : U;
-  };
-
   // reuse-cache loads: a batch takes the NB lowest units of a mask
   const auto seg_mask = [](int lo, int hi) {
     const uint64_t lo_m = (lo >= 64) ? ~0ull : ((1ull << lo) - 1);
@@ -815,16 +863,94 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
         }
   };
 
-  constexpr int ZPT = (R * 16 + NT - 1) / NT;
-  constexpr int MPWQ = (3 * GW / 16) / NW, MPWC = (GW / 16) / NW, MPWF = (FC / 16) / NW;
-  constexpr int WPP = attn_waves_per_pair(NW, HG * RB, DH / 16);
-  // fragments per wave requested ahead of each product (where registers allow)
-  constexpr int PF = ((sizeof(AT) == 4 && RB > 1) || D > 256) ? 1 : 8;
-  constexpr int NPQ = np_of<MPWQ, D / O::KF, INFL, PF>();
-  constexpr int NPC = np_of<MPWC, D / O::KF, INFL, PF>();
-  constexpr int NPF = np_of<MPWF, D / O::KF, INFL, PF>();
-  constexpr int NP2A = np_of<CBW, GW / O::KF, INFL, PF>();
-  constexpr int NP2F = np_of<CBW, FC / O::KF, INFL, PF>();
+  constexpr int MPWQ = C::m1(0), MPWC = C::m1(1), MPWF = C::m1(2), GF = C::g1(2);
+  // self-attention: one wave per SIMD (the score tile's MFMAs fill the
+  // matrix unit, and waves that share a block repeat them)
+  constexpr int WPS = attn_waves_per_pair(NW < 4 ? NW : 4, HG * RB, DH / 16);
+  constexpr int WPP = attn_waves_per_pair(NW, HG * RB, DH / 16);  // cross-attention
+  constexpr int P = C::ring_size(), K1 = C::K1;
+  static_assert(C::total(0) % P == 0 && C::total(2) % P == 0 && C::total(1) >= P, "ring");
+
+  // ---- weight streams (see Cfg)
+  const auto wrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(pk + p.pk_layers), (short)0, L * C::LAYER, 0x00020000);
+  const auto wload = [&](int soff) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16, soff, 0));
+  };
+  // a group's sequence: the runtime parts of its two stages' offsets
+  struct Seq {
+    int b1, b2;
+  };
+  const auto seq_of = [&](auto ty, int ul, int g) {
+    constexpr int TY = decltype(ty)::value;
+    return Seq{ul * C::LAYER + C::wave1(TY, w, g), ul * C::LAYER + C::wave2(TY, w, g)};
+  };
+  const auto elem = [&](auto ty, const Seq& s, int i) {
+    constexpr int TY = decltype(ty)::value;
+    return wload((i < C::s1(TY) ? s.b1 : s.b2) + C::elem(TY, i));
+  };
+  // first P elements of a unit's first sequence, requested before its LayerNorm
+  const auto fill = [&](auto ty, uint4 (&ring)[P], const Seq& s) {
+#pragma unroll
+    for (int i = 0; i < P; ++i) ring[i] = elem(ty, s, i);
+  };
+  // element i of sequence s has been multiplied: its slot takes element i +
+  // P, or one of the unit's next sequence nx (its last one ends with s again:
+  // loaded, never used)
+  const auto refill = [&](auto ty, uint4 (&ring)[P], const Seq& s, const Seq& nx, bool more, int i) {
+    constexpr int TY = decltype(ty)::value;
+    const int j = i + P;
+    if (j < C::total(TY)) ring[i % P] = elem(ty, s, j);
+    else if (j >= C::padded(TY) && more) ring[i % P] = elem(ty, nx, j - C::padded(TY));
+  };
+  // stage 1, column blocks grp * G .. + G: acc[m] = (A W^T)^T over d
+  const auto stage1 = [&](auto ty, uint4 (&ring)[P], auto& acc, int grp, const Seq& s, const Seq& nx, bool more) {
+    constexpr int TY = decltype(ty)::value, G = C::g1(TY);
+#pragma unroll
+    for (int m = 0; m < G; ++m)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) acc[m][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < K1; ++k) {
+      uint4 a[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+        a[rb] = *reinterpret_cast<const uint4*>(xa + (rb * 16 + lc) * LDA + k * O::KF + lq * O::VE);
+#pragma unroll
+      for (int m = 0; m < G; ++m) {
+        const int i = (grp * K1 + k) * G + m;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) O::mma(acc[m][rb], ring[i % P], a[rb]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < G; ++m) refill(ty, ring, s, nx, more, (grp * K1 + k) * G + m);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // stage 2: acc[c] += this wave's column blocks over the group's columns
+  const auto stage2 = [&](auto ty, uint4 (&ring)[P], auto& acc, const AT* z, const Seq& s, const Seq& nx, bool more) {
+    constexpr int TY = decltype(ty)::value;
+#pragma unroll
+    for (int k = 0; k < C::k2(TY); ++k) {
+      uint4 a[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+        a[rb] = *reinterpret_cast<const uint4*>(z + (rb * 16 + lc) * LDZ + k * O::KF + lq * O::VE);
+#pragma unroll
+      for (int c = 0; c < CBW; ++c) {
+        const int i = C::s1(TY) + k * CBW + c;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) O::mma(acc[c][rb], ring[i % P], a[rb]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < CBW; ++c) refill(ty, ring, s, nx, more, C::s1(TY) + k * CBW + c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // slots that the padded sequence leaves unused take the next one's too
+#pragma unroll
+    for (int i = C::total(TY); i < C::padded(TY); ++i) refill(ty, ring, s, nx, more, i);
+  };
 
   for (int t = 0; t < T; ++t) {
     asm volatile("" : "+v"(lane), "+v"(lc), "+v"(lq));
@@ -835,12 +961,12 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
     uint64_t evT = 0, ruT = 0;
 #pragma unroll
     for (int j = 0; j < SPT; ++j) {
-      const bool live = smp[j] >= 0;
-      const uint64_t e0 = live ? msk[(j * T + t) * 3 + 0] : 0ull;
+      const bool live = ssmp[j] >= 0;
+      const uint64_t e0 = live ? uniform64(msk[(j * T + t) * 3 + 0]) : 0ull;
       mmg[j] = (e0 & kMergedBit) != 0;
       mev[j] = e0 & ~kMergedBit;
-      mru[j] = live ? msk[(j * T + t) * 3 + 1] : 0ull;
-      mst[j] = live ? msk[(j * T + t) * 3 + 2] : 0ull;
+      mru[j] = live ? uniform64(msk[(j * T + t) * 3 + 1]) : 0ull;
+      mst[j] = live ? uniform64(msk[(j * T + t) * 3 + 2]) : 0ull;
       evT |= mev[j];
       ruT |= mru[j];
       mru_cur[j] = mru[j];
@@ -853,72 +979,39 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
         if (j == jj) v = m[jj];
       return v;
     };
-    // noise added by this step's update (prefetched)
-    // (unconditional form: always loaded from an existing slice; the last
-    // step adds none, and a dead slot's rows, which read sample 0's noise,
-    // are never output)
-    float zpre[ZPT];
+    // noise added by this step's update (prefetched; always loaded from an
+    // existing slice and action: the last step adds none, and a dead slot's
+    // rows, which read sample 0's noise, are never output)
+    f32x4 zpre[RB];
 #pragma unroll
-    for (int q = 0; q < ZPT; ++q) {
-      const int it = tid + q * NT;
-      if constexpr (UNCOND) {
-        const int itc = it < R * A ? it : 0;
-        const int row = itc / A, a = itc % A, s = smp[row / HZ];
-        const int tn = t + 1 < T ? t + 1 : T - 1;
-        zpre[q] = p.noise[(((size_t)tn * p.batch + (s >= 0 ? s : 0)) * HZ + (row % HZ)) * A + a];
-      } else {
-        zpre[q] = 0.f;
-        if (k > 0 && it < R * A) {
-          const int row = it / A, a = it % A, s = smp[row / HZ];
-          if (s >= 0) zpre[q] = p.noise[(((size_t)(t + 1) * p.batch + s) * HZ + (row % HZ)) * A + a];
-        }
-      }
+    for (int rb = 0; rb < RB; ++rb) {
+      const int row = rb * 16 + lc, s = row_sample(rb);
+      const int tn = t + 1 < T ? t + 1 : T - 1;
+      const float* zp = p.noise + (((size_t)tn * p.batch + (s >= 0 ? s : 0)) * HZ + (row % HZ)) * A;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) zpre[rb][i] = zp[4 * lq + i < A ? 4 * lq + i : 0];
     }
-    // parameters of this step's first evaluated unit (unconditional form:
-    // always, unit 0 if none; else unless the previous step requested them)
-    if constexpr (UNCOND) {
-      load_unit_params(t, evT ? __builtin_ctzll(evT) : 0);
-    } else {
-      const int f = evT ? __builtin_ctzll(evT) : U;
-      if (f < U && !(loaded_t == t && loaded_u == f)) load_unit_params(t, f);
-    }
-    // sampler constants and head bias of this step's update (prefetched)
+    // parameters of this step's first evaluated unit (unit 0 if none)
+    if constexpr (AHEAD) load_unit_params(evT ? __builtin_ctzll(evT) : 0);
+    // sampler constants of this step's update (prefetched)
     // (a lane-indexed vector load: a uniform scalar load would be waited for
     // by the next LDS access)
-    const float ddl = UNCOND ? p.ddpm[(size_t)k * 8 + (lane & 7)] : (lane < 5 ? p.ddpm[(size_t)k * 8 + lane] : 0.f);
-    float bout[ZPT];
-#pragma unroll
-    for (int q = 0; q < ZPT; ++q) {
-      const int it = tid + q * NT;
-      bout[q] = UNCOND ? raw[p.b_out + it % A] : (it < R * A ? raw[p.b_out + it % A] : 0.f);
-    }
+    const float ddl = p.ddpm[(size_t)k * 8 + (lane & 7)];
     // ---- embedding of the current sample on fp32 MFMA: h = (b_in + P_act) + x W_in^T
-    {
-      uint4 xf[RB];
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) xf[rb] = *reinterpret_cast<const uint4*>(xs + (rb * 16 + lc) * 16 + lq * 4);
+    for (int c = 0; c < CBW; ++c) {
+      uint4 wv;
+      if constexpr (EMB_LDS) wv = s_win[(w * CBW + c) * 64 + lane];
+      else if constexpr (KEEP_EMB) wv = win[c];
+      else wv = pk[p.pk_win + (size_t)(w * CBW + c) * 64 + lane];
 #pragma unroll
-      for (int c = 0; c < CBW; ++c) {
-        uint4 wv;
-        if constexpr (EMB_LDS) wv = s_win[(w * CBW + c) * 64 + lane];
-        else if constexpr (KEEP_EMB) wv = win[c];
-        else wv = pk[p.pk_win + (size_t)(w * CBW + c) * 64 + lane];
-        const int col = (w * CBW + c) * 16 + lc;
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          f32x4 acc;
-          if constexpr (PB_LDS) {
-            acc = s_pb[(w * CBW + c) * 64 + lane];
-          } else if constexpr (KEEP_EMB || EMB_LDS) {
-            acc = pb[c][rb];
-          } else {
-            const float bi = raw[p.b_in + col];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = bi + raw[p.P_act + (size_t)((rb * 16 + lq * 4 + i) % HZ) * D + col];
-          }
-          OF::mma(acc, xf[rb], wv);
-          h[c][rb] = acc;
-        }
+      for (int rb = 0; rb < RB; ++rb) {
+        f32x4 acc;
+        if constexpr (PB_LDS) acc = s_pb[(w * CBW + c) * 64 + lane];
+        else if constexpr (KEEP_EMB || EMB_LDS) acc = pb[c][rb];
+        else acc = row_bias(c, rb);
+        OF::mma(acc, wv, __builtin_bit_cast(uint4, xv[rb]));
+        h[c][rb] = acc;
       }
     }
 
@@ -948,39 +1041,21 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
       // ---- evaluate unit e for the tile
       asm volatile("" : "+v"(lane), "+v"(lc), "+v"(lq));
       const int l = e / 3, u = e - 3 * l;
-      const LayerOff lo = s_loff[l];
-      const PackOff po = s_poff[l];
-      float lg[CBW], lb[CBW], rbias[CBW];
+      const int lp = l * C::PLAYER;
+      f32x4 lg[CBW], lb[CBW], rbias[CBW];
+      if constexpr (AHEAD) {
 #pragma unroll
-      for (int c = 0; c < CBW; ++c) {
-        lg[c] = nlg[c];
-        lb[c] = nlb[c];
-        rbias[c] = nrb[c];
-      }
-      // request the parameters of the next evaluated unit (this step or the
-      // next) now, so that they have the whole unit to arrive
-      const auto request_next_params = [&]() {
-        const uint64_t later = (e + 1 < 64) ? (evT >> (e + 1)) : 0ull;
-        if constexpr (UNCOND) {
-          // this unit's own parameters again when no later unit of the
-          // step is evaluated (the next step loads its first)
-          load_unit_params(t, later ? e + 1 + __builtin_ctzll(later) : e);
-        } else if (later) load_unit_params(t, e + 1 + __builtin_ctzll(later));
-        else if (t + 1 < T) {
-          const int f = first_eval(t + 1);
-          if (f < U) load_unit_params(t + 1, f);
+        for (int c = 0; c < CBW; ++c) {
+          lg[c] = nlg[c];
+          lb[c] = nlb[c];
+          rbias[c] = nrb[c];
         }
-      };
-      request_next_params();
-      const auto gcb_sa = [&](int g) {
-        return [=](int m) {
-          const int iloc = w + NW * m, part = iloc / (GW / 16), within = iloc % (GW / 16);
-          return part * CB + g * (GW / 16) + within;
-        };
-      };
-      const auto gcb_ca = [&](int g) { return [=](int m) { return g * (GW / 16) + w + NW * m; }; };
-      const auto gcb_ff = [&](int ch) { return [=](int m) { return ch * (FC / 16) + w + NW * m; }; };
-      const auto own = [&](int m) { return w * CBW + m; };
+        // request the parameters of the step's next evaluated unit now, so
+        // that they have the whole unit to arrive (this unit's own again when
+        // no later unit is evaluated: the next step loads its first)
+        const uint64_t later = (e + 1 < 64) ? (evT >> (e + 1)) : 0ull;
+        load_unit_params(later ? e + 1 + __builtin_ctzll(later) : e);
+      }
       f32x4 r[CBW][RB];
 #pragma unroll
       for (int c = 0; c < CBW; ++c)
@@ -988,116 +1063,105 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
         for (int rb = 0; rb < RB; ++rb) r[c][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
       // LayerNorm of the unit's input into the stage-1 operand buffer
       const auto layer_norm_to_xa = [&]() {
-        float mu[RB][4], rs[RB][4];
+        if constexpr (!AHEAD) {
+          load_unit_params(e);
+#pragma unroll
+          for (int c = 0; c < CBW; ++c) {
+            lg[c] = nlg[c];
+            lb[c] = nlb[c];
+          }
+        }
+        float mu[RB], rs[RB];
         ln_stats<C>(h, red, mu, rs, w, lc, lq);
 #pragma unroll
-        for (int c = 0; c < CBW; ++c) {
-          const int col = (w * CBW + c) * 16 + lc;
+        for (int c = 0; c < CBW; ++c)
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              O::store(xa, LDA, rb * 16 + lq * 4 + i, col, (h[c][rb][i] - mu[rb][i]) * rs[rb][i] * lg[c] + lb[c]);
-        }
+            O::store4(xa, LDA, rb * 16 + lc, (w * CBW + c) * 16 + lq * 4, (h[c][rb] - mu[rb]) * rs[rb] * lg[c] + lb[c]);
         __syncthreads();
       };
 
       if (u == 0) {
         // ---------------- self-attention unit (causal over the action tokens)
-        uint4 b1q[NPQ][MPWQ];  // stage-1 weights of the first chunk, requested before the LayerNorm
-        gemm_pref<NPQ, MPWQ>(b1q, pk + po.qkv, D / O::KF, 0, gcb_sa(member), lane);
+        const std::integral_constant<int, 0> ty;
+        uint4 ring[P];
+        fill(ty, ring, seq_of(ty, l, member));
         layer_norm_to_xa();
         for (int g = member; g < NH / HG; g += TEAM) {
           asm volatile("" : "+v"(lane), "+v"(lc), "+v"(lq));
+          constexpr bool more = NH / HG > TEAM;
+          const Seq s = seq_of(ty, l, g), nx = seq_of(ty, l, g + TEAM < NH / HG ? g + TEAM : g);
           f32x4 y[MPWQ][RB];
+          f32x4 bq[MPWQ];  // stage-1 biases, requested before the GEMM so their latency is hidden
+#pragma unroll
+          for (int m = 0; m < MPWQ; ++m)
+            bq[m] = lparam(lp + C::pBQKV + ((NW * m) / (GW / 16) * CB + (NW * m) % (GW / 16) + g * (GW / 16) + w) * 16);
+          stage1(ty, ring, y, 0, s, nx, more);
 #pragma unroll
           for (int m = 0; m < MPWQ; ++m)
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) y[m][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-          float bq[MPWQ];  // stage-1 biases, requested before the GEMM so their latency is hidden
-#pragma unroll
-          for (int m = 0; m < MPWQ; ++m) bq[m] = raw[lo.b_qkv + gcb_sa(g)(m) * 16 + lc];
-          gemm_run<AT, RB, MPWQ, D / O::KF, INFL, NPQ>(y, xa, LDA, pk + po.qkv, D / O::KF, 0, gcb_sa(g), lane, b1q);
-          uint4 b2[NP2A][CBW];
-          gemm_pref<NP2A, CBW>(b2, pk + po.o, D / O::KF, g * (GW / O::KF), own, lane);
-#pragma unroll
-          for (int m = 0; m < MPWQ; ++m) {
-            const int loc = (w + NW * m) * 16 + lc;
-#pragma unroll
             for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) ybuf[(rb * 16 + lq * 4 + i) * LDY + loc] = y[m][rb][i] + bq[m];
-          }
+              *reinterpret_cast<f32x4*>(ybuf + (rb * 16 + lc) * LDY + (w + NW * m) * 16 + lq * 4) = y[m][rb] + bq[m];
           __syncthreads();
-          // scores, softmax and values on fp32 MFMA tiles: WPP waves per
-          // (head, query block), each with DH / 16 / WPP value column blocks
-          for (int it = w; it < HG * RB * WPP; it += NW) {
-            const int pr = it / WPP, part = it % WPP;
+          // scores, softmax and values on fp32 MFMA tiles: WPS waves per
+          // (head, query block), each with DH / 16 / WPS value column blocks.
+          // The lane's scores of its query against keys 4 lq .. + 3 are the
+          // second operand of the value product as they stand (step i takes
+          // key 4 lq + i of every lane group).
+          for (int it = w; it < HG * RB * WPS; it += NW) {
+            const int pr = it / WPS, part = it % WPS;
             const int hh = pr % HG, ib = pr / HG;
             const int jb0 = (HZ >= 16) ? ((ib * 16) / HZ) * (HZ / 16) : ib;
+            const int gi = ib * 16 + lc;  // query row
             f32x4 s[NJB];
+            float m = -INFINITY;
 #pragma unroll
             for (int jj = 0; jj < NJB; ++jj) {
               s[jj] = f32x4{0.f, 0.f, 0.f, 0.f};
               const int jb = jb0 + jj;
               if (jb <= ib)
-                s[jj] = qk_tile<DH>(ybuf + (ib * 16 + lc) * LDY + hh * DH, ybuf + (jb * 16 + lc) * LDY + GW + hh * DH,
-                                    true, lq);
-            }
-            float sm[4];
+                s[jj] = qk_tile<DH>(ybuf + (ib * 16 + lc) * LDY + hh * DH, ybuf + (jb * 16 + lc) * LDY + GW + hh * DH, lq);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int gi = ib * 16 + lq * 4 + i;
-              float m = -INFINITY;
-#pragma unroll
-              for (int jj = 0; jj < NJB; ++jj) {
-                const int gj = (jb0 + jj) * 16 + lc;
+              for (int i = 0; i < 4; ++i) {
+                const int gj = jb * 16 + lq * 4 + i;
                 const bool ok = (gj <= gi) && (gj / HZ == gi / HZ);
                 s[jj][i] = ok ? s[jj][i] * (kScale * kLog2e) : -INFINITY;
                 m = fmaxf(m, s[jj][i]);
               }
-              m = row16_max(m);
-              float su = 0.f;
+            }
+            m = quad_rows_max(m);
+            float su = 0.f;
 #pragma unroll
-              for (int jj = 0; jj < NJB; ++jj) {
+            for (int jj = 0; jj < NJB; ++jj)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
                 const float ev = (s[jj][i] == -INFINITY) ? 0.f : fast_exp2(s[jj][i] - m);
                 s[jj][i] = ev;
                 su += ev;
               }
-              sm[i] = row16_sum(su);
-            }
-            float* sc = pw + w * PWN;
+            const float inv = fast_rcp(quad_rows_sum(su));
 #pragma unroll
-            for (int jj = 0; jj < NJB; ++jj)
+            for (int jj = 0; jj < NJB; ++jj) s[jj] *= inv;
 #pragma unroll
-              for (int i = 0; i < 4; ++i) sc[(jj * 16 + lq * 4 + i) * PS + lc] = s[jj][i] * fast_rcp(sm[i]);
-            wave_lds_sync();
-#pragma unroll
-            for (int cbi = 0; cbi < DH / 16 / WPP; ++cbi) {
-              const int cb = part * (DH / 16 / WPP) + cbi;
+            for (int cbi = 0; cbi < DH / 16 / WPS; ++cbi) {
+              const int cb = part * (DH / 16 / WPS) + cbi;
               f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
               for (int jj = 0; jj < NJB; ++jj) {
                 const int jb = jb0 + jj;
                 if (jb <= ib) {
 #pragma unroll
-                  for (int kk = 0; kk < 4; ++kk) {
-                    const float a = sc[(jj * 16 + lc) * PS + 4 * kk + lq];
-                    const float v = ybuf[(jb * 16 + 4 * kk + lq) * LDY + 2 * GW + hh * DH + cb * 16 + lc];
-                    o = mfma4(a, v, o);
+                  for (int i = 0; i < 4; ++i) {
+                    const float v = ybuf[(jb * 16 + 4 * lq + i) * LDY + 2 * GW + hh * DH + cb * 16 + lc];
+                    o = mfma4(v, s[jj][i], o);
                   }
                 }
               }
-#pragma unroll
-              for (int i = 0; i < 4; ++i) O::store(zbuf, LDZ, ib * 16 + lq * 4 + i, hh * DH + cb * 16 + lc, o[i]);
+              O::store4(zbuf, LDZ, ib * 16 + lc, hh * DH + cb * 16 + lq * 4, o);
             }
-            wave_lds_sync();
           }
-          // the next head group's first stage-1 k-steps stream in during this output product
-          if (g + TEAM < NH / HG) gemm_pref<NPQ, MPWQ>(b1q, pk + po.qkv, D / O::KF, 0, gcb_sa(g + TEAM), lane);
           __syncthreads();
-          gemm_run<AT, RB, CBW, GW / O::KF, INFL, NP2A>(r, zbuf, LDZ, pk + po.o, D / O::KF, g * (GW / O::KF), own, lane,
-                                                       b2);
+          stage2(ty, ring, r, zbuf, s, nx, more);
         }
       } else if (C::FOLD && fold && u == 1) {
         if constexpr (C::FOLD) {
@@ -1105,130 +1169,96 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
           // Score columns n = j * NH + h (memory token j, head h) of the row
           // block's sample, padded to 16 with zero columns.  Every team
           // member evaluates the whole unit (no partials to exchange).
-          constexpr int KPW = (D / O::KF) / NW, VQ = O::VE / 4, SJ = 16 / NH;
-          static_assert(KPW * NW == D / O::KF && SJ * NH == 16, "folded cross-attention split");
+          constexpr int KPW = (D / O::KF) / NW, VQ = O::VE / 4;
+          static_assert(KPW * NW == D / O::KF && NH == 4, "folded cross-attention split");
           const float* trec = p.tfold + ((size_t)k * L + l) * REC;
           // record of memory token j of the sample in row block rb, and
-          // whether it exists (else the time-token record stands in and the
-          // loaded values are replaced by zeros)
+          // whether it exists (else the time-token record stands in)
           const auto rec = [&](int rb, int j, bool& ok) -> const float* {
-            const int s_ = smp[(rb * 16) / HZ];
+            const int s_ = row_sample(rb);
             ok = s_ >= 0 && j < S;
             return (ok && j > 0) ? okv + (((size_t)s_ * L + l) * nobs + (j - 1)) * REC : trec;
           };
-          const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-          // u columns of this wave's k-range (the B operand of the scores)
-          // (loaded values are zeroed where they do not exist only at their
-          // use, after the LayerNorm, so that no wait for them sits before
-          // its barriers)
+          // u columns of this wave's k-range (lane: column lc, memory token
+          // lc / NH of head lc % NH; columns of tokens that do not exist read
+          // the time token's record and are masked in the softmax)
           f32x4 ub[RB][KPW][VQ];
-          bool ubok[RB];
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb) {
-            const float* q = rec(rb, lc / NH, ubok[rb]) + (lc % NH) * D + w * KPW * O::KF + lq * O::VE;
+            bool ok;
+            const float* q = rec(rb, lc / NH, ok) + (lc % NH) * D + w * KPW * O::KF + lq * O::VE;
 #pragma unroll
             for (int kf = 0; kf < KPW; ++kf)
 #pragma unroll
               for (int v = 0; v < VQ; ++v) ub[rb][kf][v] = *reinterpret_cast<const f32x4*>(q + kf * O::KF + 4 * v);
           }
-          // w vectors of the row blocks' samples, staged through LDS
-          constexpr int WQN = RB * 16 * D / 4, WQ = (WQN + NT - 1) / NT;
-          f32x4 wv[WQ];
-          bool wvok[WQ];
-#pragma unroll
-          for (int q = 0; q < WQ; ++q) {
-            const int it = tid + q * NT;
-            const int f = it * 4, rb = f / (16 * D), n = (f / D) % 16, c = f % D;
-            bool ok = false;
-            const float* src = it < WQN ? rec(rb, n / NH, ok) : trec;
-            wv[q] = *reinterpret_cast<const f32x4*>(src + NH * D + (n % NH) * D + c);
-            wvok[q] = it < WQN && ok;
-          }
-          // c terms of the softmax thread's (row, head)
-          float cqv[SJ];
-          bool cqok[SJ];
-          {
-            const int r = tid / NH, hd = tid % NH;
-#pragma unroll
-            for (int j = 0; j < SJ; ++j) {
-              bool ok = false;
-              const float* src = tid < R * NH ? rec(r >> 4, j, ok) : trec;
-              cqv[j] = src[2 * NH * D + hd];
-              cqok[j] = tid < R * NH && ok;
-            }
-          }
-          layer_norm_to_xa();
-          // partial scores over this wave's k-range on MFMA
-          float* const sb = ybuf;                    // [NW][RB][64 lanes][4]
-          float* const pb = ybuf + NW * RB * 256;    // [16][R] probabilities (column n, row)
-          float* const wst = pb + 16 * R;            // [RB][16][D] w vectors
+          // c terms of memory token lq (heads 0 .. 3) and its w vectors at
+          // this wave's columns (the first operand of the output product)
+          f32x4 cq[RB];
+          bool cok[RB];
+          f32x4 wv[RB][CBW];
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb) {
-            f32x4 acc = zero4;
+            const float* q = rec(rb, lq, cok[rb]) + NH * D;
+            cq[rb] = *reinterpret_cast<const f32x4*>(q + NH * D);
+#pragma unroll
+            for (int c = 0; c < CBW; ++c)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) wv[rb][c][i] = q[i * D + (w * CBW + c) * 16 + lc];
+          }
+          layer_norm_to_xa();
+          // partial scores over this wave's k-range on MFMA (lane: row lc,
+          // columns 4 lq .. + 3, i.e. memory token lq of the four heads)
+          float* const sb = ybuf;  // [RB][NW][64 lanes][4]
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kf = 0; kf < KPW; ++kf) {
               const uint4 a =
                   *reinterpret_cast<const uint4*>(xa + (rb * 16 + lc) * LDA + (w * KPW + kf) * O::KF + lq * O::VE);
               uint4 bq;
               if constexpr (sizeof(AT) == 2) {
-                const f32x4 x0 = ubok[rb] ? ub[rb][kf][0] : zero4, x1 = ubok[rb] ? ub[rb][kf][1] : zero4;
+                const f32x4 x0 = ub[rb][kf][0], x1 = ub[rb][kf][1];
                 bq.x = bf16x2_rne(x0[0], x0[1]);
                 bq.y = bf16x2_rne(x0[2], x0[3]);
                 bq.z = bf16x2_rne(x1[0], x1[1]);
                 bq.w = bf16x2_rne(x1[2], x1[3]);
               } else {
-                bq = __builtin_bit_cast(uint4, ubok[rb] ? ub[rb][kf][0] : zero4);
+                bq = __builtin_bit_cast(uint4, ub[rb][kf][0]);
               }
-              O::mma(acc, a, bq);
+              O::mma(acc, bq, a);
             }
-            *reinterpret_cast<f32x4*>(sb + ((w * RB + rb) * 64 + lane) * 4) = acc;
-          }
-#pragma unroll
-          for (int q = 0; q < WQ; ++q)
-            if (tid + q * NT < WQN) *reinterpret_cast<f32x4*>(wst + (tid + q * NT) * 4) = wvok[q] ? wv[q] : zero4;
-          __syncthreads();
-          // softmax over the memory tokens of each (row, head)
-          if (tid < R * NH) {
-            const int r = tid / NH, hd = tid % NH, rb = r >> 4, rr = r & 15;
-            float sc[SJ], mx = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < SJ; ++j) {
-              const int n = j * NH + hd;
-              float a = 0.f;
-#pragma unroll
-              for (int ww = 0; ww < NW; ++ww) a += sb[((ww * RB + rb) * 64 + (rr >> 2) * 16 + n) * 4 + (rr & 3)];
-              sc[j] = j < S ? (a + (cqok[j] ? cqv[j] : 0.f)) * (kScale * kLog2e) : -INFINITY;
-              mx = fmaxf(mx, sc[j]);
-            }
-            float den = 0.f;
-#pragma unroll
-            for (int j = 0; j < SJ; ++j) {
-              sc[j] = j < S ? fast_exp2(sc[j] - mx) : 0.f;
-              den += sc[j];
-            }
-            const float inv = fast_rcp(den);
-#pragma unroll
-            for (int j = 0; j < SJ; ++j) pb[(j * NH + hd) * R + r] = sc[j] * inv;
+            *reinterpret_cast<f32x4*>(sb + ((rb * NW + w) * 64 + lane) * 4) = acc;
           }
           __syncthreads();
-          // output: r = P W over the 16 columns (padding columns are zero),
-          // four k-steps of fp32 MFMA per column block
+          // every wave sums the partials, takes the softmax over the memory
+          // tokens (lane groups lq) of each head and forms its own columns of
+          // the output, r = P W over the 16 columns
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb) {
-            float pa[4];
+            f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) pa[kk] = pb[(4 * kk + lq) * R + rb * 16 + lc];
+            for (int ww = 0; ww < NW; ++ww) a += *reinterpret_cast<const f32x4*>(sb + ((rb * NW + ww) * 64 + lane) * 4);
+            f32x4 pr;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float sc = lq < S ? (a[i] + (cok[rb] ? cq[rb][i] : 0.f)) * (kScale * kLog2e) : -INFINITY;
+              const float mx = quad_rows_max(sc);  // (all lanes take part in the swaps)
+              const float ev = lq < S ? fast_exp2(sc - mx) : 0.f;
+              pr[i] = ev * fast_rcp(quad_rows_sum(ev));
+            }
 #pragma unroll
             for (int c = 0; c < CBW; ++c)
 #pragma unroll
-              for (int kk = 0; kk < 4; ++kk)
-                r[c][rb] = mfma4(pa[kk], wst[(rb * 16 + 4 * kk + lq) * D + (w * CBW + c) * 16 + lc], r[c][rb]);
+              for (int i = 0; i < 4; ++i) r[c][rb] = mfma4(wv[rb][c][i], pr[i], r[c][rb]);
           }
         }
       } else if (u == 1) {
         // ---------------- cross-attention unit (time token + observation tokens)
-        uint4 b1c[NPC][MPWC];
-        gemm_pref<NPC, MPWC>(b1c, pk + po.q, D / O::KF, 0, gcb_ca(member), lane);
+        const std::integral_constant<int, 1> ty;
+        uint4 ring[P];
+        fill(ty, ring, seq_of(ty, l, member));
         // memory keys/values of a head group: time token + observation tokens
         constexpr int KVN = SPT * SMAX * 2 * GW, KVQ = (KVN + NT - 1) / NT;
         float kvv[KVQ];
@@ -1258,25 +1288,19 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
         for (int g = member; g < NH / HG; g += TEAM) {
           asm volatile("" : "+v"(lane), "+v"(lc), "+v"(lq));
           if (g != member) load_kv(g);
+          constexpr bool more = NH / HG > TEAM;
+          const Seq s = seq_of(ty, l, g), nx = seq_of(ty, l, g + TEAM < NH / HG ? g + TEAM : g);
           f32x4 y[MPWC][RB];
+          f32x4 bq[MPWC];
+#pragma unroll
+          for (int m = 0; m < MPWC; ++m)
+            bq[m] = lparam(lp + C::pBQ + (g * (GW / 16) + w + NW * m) * 16);
+          stage1(ty, ring, y, 0, s, nx, more);
 #pragma unroll
           for (int m = 0; m < MPWC; ++m)
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) y[m][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-          float bq[MPWC];
-#pragma unroll
-          for (int m = 0; m < MPWC; ++m) bq[m] = raw[lo.b_q + gcb_ca(g)(m) * 16 + lc];
-          gemm_run<AT, RB, MPWC, D / O::KF, INFL, NPC>(y, xa, LDA, pk + po.q, D / O::KF, 0, gcb_ca(g), lane, b1c);
-          uint4 b2[NP2A][CBW];
-          gemm_pref<NP2A, CBW>(b2, pk + po.o2, D / O::KF, g * (GW / O::KF), own, lane);
-#pragma unroll
-          for (int m = 0; m < MPWC; ++m) {
-            const int loc = (w + NW * m) * 16 + lc;
-#pragma unroll
             for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) ybuf[(rb * 16 + lq * 4 + i) * LDY + loc] = y[m][rb][i] + bq[m];
-          }
+              *reinterpret_cast<f32x4*>(ybuf + (rb * 16 + lc) * LDY + (w + NW * m) * 16 + lq * 4) = y[m][rb] + bq[m];
 #pragma unroll
           for (int q = 0; q < KVQ; ++q)
             if (tid + q * NT < KVN) kvbuf[tid + q * NT] = kvok[q] ? kvv[q] : 0.f;
@@ -1326,50 +1350,58 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
             }
             const float inv = fast_rcp(den);
 #pragma unroll
-            for (int d = 0; d < OD; ++d) O::store(zbuf, LDZ, row, c0 + d, o[d] * inv);
+            for (int d = 0; d < OD; d += 4)
+              O::store4(zbuf, LDZ, row, c0 + d, f32x4{o[d] * inv, o[d + 1] * inv, o[d + 2] * inv, o[d + 3] * inv});
           }
-          if (g + TEAM < NH / HG) gemm_pref<NPC, MPWC>(b1c, pk + po.q, D / O::KF, 0, gcb_ca(g + TEAM), lane);
           __syncthreads();
-          gemm_run<AT, RB, CBW, GW / O::KF, INFL, NP2A>(r, zbuf, LDZ, pk + po.o2, D / O::KF, g * (GW / O::KF), own,
-                                                       lane, b2);
+          stage2(ty, ring, r, zbuf, s, nx, more);
         }
       } else {
         // ---------------- feed-forward unit, d_ff streamed in chunks of FC
-        uint4 b1f[NPF][MPWF];
-        gemm_pref<NPF, MPWF>(b1f, pk + po.w1, D / O::KF, 0, gcb_ff(member), lane);
+        const std::integral_constant<int, 2> ty;
+        uint4 ring[P];
+        fill(ty, ring, seq_of(ty, l, member));
         layer_norm_to_xa();
         for (int ch = member; ch < DFF / FC; ch += TEAM) {
           asm volatile("" : "+v"(lane), "+v"(lc), "+v"(lq));
+          constexpr bool more = DFF / FC > TEAM;
+          const Seq s = seq_of(ty, l, ch), nx = seq_of(ty, l, ch + TEAM < DFF / FC ? ch + TEAM : ch);
           AT* const zb = zbuf + (ZB2 ? (((ch - member) / TEAM) & 1) * (R * LDZ) : 0);
-          f32x4 y[MPWF][RB];
+          // biases of a pair of column blocks, requested one pair ahead
+          const auto bias = [&](int m) { return lparam(lp + C::pB1 + ch * FC + (w + NW * m) * 16); };
+          f32x4 bn[GF];
 #pragma unroll
-          for (int m = 0; m < MPWF; ++m)
+          for (int m = 0; m < GF; ++m) bn[m] = bias(m);
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) y[m][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-          float b1v[MPWF];
+          for (int grp = 0; grp < MPWF / GF; ++grp) {
+            f32x4 y[GF][RB], b1v[GF];
 #pragma unroll
-          for (int m = 0; m < MPWF; ++m) b1v[m] = raw[lo.b_1 + ch * FC + (w + NW * m) * 16 + lc];
-          gemm_run<AT, RB, MPWF, D / O::KF, INFL, NPF>(y, xa, LDA, pk + po.w1, D / O::KF, 0, gcb_ff(ch), lane, b1f);
-          uint4 b2[NP2F][CBW];
-          gemm_pref<NP2F, CBW>(b2, pk + po.w2, DFF / O::KF, ch * (FC / O::KF), own, lane);
+            for (int m = 0; m < GF; ++m) {
+              b1v[m] = bn[m];
+              if (grp + 1 < MPWF / GF) bn[m] = bias((grp + 1) * GF + m);
+            }
+            stage1(ty, ring, y, grp, s, nx, more);
 #pragma unroll
-          for (int m = 0; m < MPWF; ++m) {
-            const int loc = (w + NW * m) * 16 + lc;
+            for (int m = 0; m < GF; ++m)
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
+              for (int rb = 0; rb < RB; ++rb) {
+                f32x4 v = y[m][rb] + b1v[m];
 #pragma unroll
-              for (int i = 0; i < 4; ++i)
-                O::store(zb, LDZ, rb * 16 + lq * 4 + i, loc, gelu_erf(y[m][rb][i] + b1v[m]));
+                for (int i = 0; i < 4; ++i) v[i] = gelu_erf(v[i]);
+                O::store4(zb, LDZ, rb * 16 + lc, (w + NW * (grp * GF + m)) * 16 + lq * 4, v);
+              }
           }
-          // the next chunk's first stage-1 k-steps stream in during this chunk's second product
-          if (ch + TEAM < DFF / FC) gemm_pref<NPF, MPWF>(b1f, pk + po.w1, D / O::KF, 0, gcb_ff(ch + TEAM), lane);
           __syncthreads();
-          gemm_run<AT, RB, CBW, FC / O::KF, INFL, NP2F>(r, zb, LDZ, pk + po.w2, DFF / O::KF, ch * (FC / O::KF), own,
-                                                        lane, b2);
+          stage2(ty, ring, r, zb, s, nx, more);
           // (with one buffer, the next chunk's GELU outputs wait for every
           // wave's reads of this one)
-          if constexpr (!ZB2) __syncthreads();
+          if constexpr (!ZB2 && DFF / FC > TEAM) __syncthreads();
         }
+      }
+      if constexpr (!AHEAD) {  // requested here, added after the exchange
+        const int ro = lp + w * CBW * 16 + (u == 0 ? C::pBO : (u == 1 ? C::pBO2 : C::pB2));
+#pragma unroll
+        for (int c = 0; c < CBW; ++c) rbias[c] = lparam(ro + c * 16);
       }
       if constexpr (TEAM > 1) if (!(fold && u == 1)) {
         // Sum the members' partial residuals in member order, so that every
@@ -1558,9 +1590,8 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
             h[c][rb] += v;
             if (p.acts != nullptr && member == 0) {
               // activation record of the uncached policy (Sec. 3.3): a[sample][unit][step][H][d]
-              float* ap = p.acts + (((size_t)smp[j] * U + e) * T + t) * (HZ * D) + (w * CBW + c) * 16 + lc;
-#pragma unroll
-              for (int i = 0; i < 4; ++i) ap[(size_t)((rb * 16 + lq * 4 + i) % HZ) * D] = v[i];
+              *reinterpret_cast<f32x4*>(p.acts + (((size_t)smp[j] * U + e) * T + t) * (HZ * D) +
+                                        (size_t)((rb * 16 + lc) % HZ) * D + (w * CBW + c) * 16 + lq * 4) = v;
             }
           } else if (pick(mru, j) & bit) {
             h[c][rb] += cload(e, c, rb);
@@ -1571,77 +1602,61 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
 
     // ---- head (final LayerNorm + linear on fp32 MFMA) and DDPM update
     {
-      float mu[RB][4], rs[RB][4];
+      float mu[RB], rs[RB];
       ln_stats<C>(h, red, mu, rs, w, lc, lq);
       f32x4 eacc[RB];
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) eacc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      float* sc = pw + w * PWN;
 #pragma unroll
       for (int c = 0; c < CBW; ++c) {
-        float g_, b_;
+        f32x4 g_, b_;
+        const int col = (w * CBW + c) * 16 + lq * 4;
         if constexpr (EMB_LDS) {
-          g_ = s_lf[(w * CBW + c) * 16 + lc];
-          b_ = s_lf[D + (w * CBW + c) * 16 + lc];
+          g_ = *reinterpret_cast<const f32x4*>(s_lf + col);
+          b_ = *reinterpret_cast<const f32x4*>(s_lf + D + col);
         } else if constexpr (KEEP_EMB) {
           g_ = lfg[c];
           b_ = lfb[c];
         } else {
-          const int col = (w * CBW + c) * 16 + lc;
-          g_ = raw[p.lnf_g + col];
-          b_ = raw[p.lnf_b + col];
+          g_ = *reinterpret_cast<const f32x4*>(raw + p.lnf_g + col);
+          b_ = *reinterpret_cast<const f32x4*>(raw + p.lnf_b + col);
         }
         uint4 wo;
         if constexpr (EMB_LDS) wo = s_wout[(w * CBW + c) * 64 + lane];
         else if constexpr (KEEP_EMB) wo = wout[c];
         else wo = pk[p.pk_wout + (size_t)(w * CBW + c) * 64 + lane];
+        // the normalised columns are the second operand as they stand
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            sc[(rb * 16 + lq * 4 + i) * PS + lc] = (h[c][rb][i] - mu[rb][i]) * rs[rb][i] * g_ + b_;
-        wave_lds_sync();
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          const float* ar = sc + (rb * 16 + lc) * PS + lq;
-          eacc[rb] = mfma4(ar[0], __uint_as_float(wo.x), eacc[rb]);
-          eacc[rb] = mfma4(ar[4], __uint_as_float(wo.y), eacc[rb]);
-          eacc[rb] = mfma4(ar[8], __uint_as_float(wo.z), eacc[rb]);
-          eacc[rb] = mfma4(ar[12], __uint_as_float(wo.w), eacc[rb]);
-        }
-        wave_lds_sync();
+          OF::mma(eacc[rb], wo, __builtin_bit_cast(uint4, (h[c][rb] - mu[rb]) * rs[rb] * g_ + b_));
       }
-      float* epsp = ybuf;  // [NW][R][16] partial products of this wave's columns
+      // partial noise estimates of the waves' columns, summed by every wave
+      // for the actions its lanes keep
+      float* epsp = ybuf;  // [RB][NW][64 lanes][4]
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) epsp[(w * R + rb * 16 + lq * 4 + i) * 16 + lc] = eacc[rb][i];
+      for (int rb = 0; rb < RB; ++rb) *reinterpret_cast<f32x4*>(epsp + ((rb * NW + w) * 64 + lane) * 4) = eacc[rb];
       __syncthreads();
+      const auto dd = [&](int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ddl), i)); };
+      const float s1 = dd(0), rsa = dd(1), c0 = dd(2), ct = dd(3), sg = dd(4);
 #pragma unroll
-      for (int q = 0; q < ZPT; ++q) {
-        const int it = tid + q * NT;
-        if (it < R * A) {
-          const int row = it / A, a = it % A;
-          float part = 0.f;
+      for (int rb = 0; rb < RB; ++rb) {
+        f32x4 part = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int ww = 0; ww < NW; ++ww) part += epsp[(ww * R + row) * 16 + a];
-          const float e = bout[q] + part;
-          const auto dd = [&](int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ddl), i)); };
-          const float s1 = dd(0), rsa = dd(1), c0 = dd(2), ct = dd(3), sg = dd(4);
-          float* xp = xs + row * 16 + OF::pcol(a);
-          const float x = *xp;
+        for (int ww = 0; ww < NW; ++ww) part += *reinterpret_cast<const f32x4*>(epsp + ((rb * NW + ww) * 64 + lane) * 4);
+        const int row = rb * 16 + lc, s = row_sample(rb);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float e = bout[i] + part[i], x = xv[rb][i];
           float x0 = (x - s1 * e) * rsa;
           if (p.clip) x0 = fminf(fmaxf(x0, -1.f), 1.f);
           float xn = c0 * x0 + ct * x;
-          if (k > 0) xn += sg * zpre[q];
-          *xp = xn;
-          if (t == T - 1) {
-            const int s = smp[row / HZ];
-            if (s >= 0 && member == 0) p.out[((size_t)s * HZ + (row % HZ)) * A + a] = xn;
-          }
+          if (k > 0) xn += sg * zpre[rb][i];
+          const int a = 4 * lq + i;
+          xv[rb][i] = a < A ? xn : 0.f;
+          if (t == T - 1 && w == 0 && a < A && s >= 0 && member == 0)
+            p.out[((size_t)s * HZ + (row % HZ)) * A + a] = xn;
         }
       }
-      __syncthreads();
     }
   }
 }
@@ -1682,13 +1697,12 @@ __global__ void __launch_bounds__(512) obs_fold_kernel(const KParams p) {
   }
 #pragma unroll
   for (int m = 0; m < MPWO; ++m) {
-    const int gcol = (w + NW * m) * 16 + lc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = lq * 4 + i, o = (row0 + row) % nobs;
-      const float v = row < nrows ? acc[m][0][i] + raw[p.b_obs + gcol] + raw[p.P_mem + (size_t)(1 + o) * D + gcol] : 0.f;
-      O::store(xa, LDA, row, gcol, v);
-    }
+    const int gcol = (w + NW * m) * 16 + lq * 4, o = (row0 + lc) % nobs;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (lc < nrows)
+      v = acc[m][0] + *reinterpret_cast<const f32x4*>(raw + p.b_obs + gcol) +
+          *reinterpret_cast<const f32x4*>(raw + p.P_mem + (size_t)(1 + o) * D + gcol);
+    O::store4(xa, LDA, lc, gcol, v);
   }
   __syncthreads();
   const LayerOff lo = p.loff[l];
@@ -1700,9 +1714,8 @@ __global__ void __launch_bounds__(512) obs_fold_kernel(const KParams p) {
                                     [&](int m) { return w + NW * m; }, lane);
 #pragma unroll
   for (int m = 0; m < MPWK; ++m) {
-    const int gcol = (w + NW * m) * 16 + lc;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) kvr[(lq * 4 + i) * (2 * D) + gcol] = kv[m][0][i] + raw[lo.b_kv + gcol];
+    const int gcol = (w + NW * m) * 16 + lq * 4;
+    *reinterpret_cast<f32x4*>(kvr + lc * (2 * D) + gcol) = kv[m][0] + *reinterpret_cast<const f32x4*>(raw + lo.b_kv + gcol);
   }
   __syncthreads();
   fold_rows<D, DH, NT, 16, sizeof(AT) == 2>(
@@ -1746,7 +1759,7 @@ __global__ void pack_kernel(const float* __restrict__ raw, size_t off, int N, in
       }
     } else {
       for (int j = 0; j < 4; ++j) {
-        const int kk = kb * 16 + 4 * j + q;
+        const int kk = kb * 16 + 4 * q + j;
         e[j] = kk < K ? __float_as_uint(W[kk]) : 0u;
       }
     }
@@ -1881,13 +1894,13 @@ hipError_t launch_ddpm_table(int T, float* table, hipStream_t stream) {
   X(__bf16, 64, 32, 8, 2, 256, 4, 2, 256, 8, 1)           \
   X(float, 256, 64, 16, 1, 1024, 8, 4, 256, 8, 1)         \
   X(float, 256, 64, 16, 2, 1024, 8, 2, 128, 8, 1)         \
-  X(__bf16, 256, 64, 16, 1, 1024, 8, 4, 256, 8, 1)        \
+  X(__bf16, 256, 64, 16, 1, 1024, 8, 4, 1024, 8, 1)       \
   X(__bf16, 256, 64, 16, 2, 1024, 8, 2, 256, 8, 1)        \
   X(__bf16, 768, 64, 32, 1, 3072, 8, 2, 256, 5, 1)        \
   X(float, 256, 64, 16, 1, 1024, 4, 1, 256, 8, 4)         \
   X(__bf16, 256, 64, 16, 1, 1024, 4, 1, 256, 8, 4)        \
   X(float, 256, 64, 16, 1, 1024, 8, 2, 256, 8, 2)         \
-  X(__bf16, 256, 64, 16, 1, 1024, 8, 2, 256, 8, 2)        \
+  X(__bf16, 256, 64, 16, 1, 1024, 8, 2, 512, 8, 2)        \
   X(__bf16, 768, 64, 32, 1, 3072, 8, 2, 256, 5, 2)
 
 template <class AT> constexpr int dtype_of() { return std::is_same<AT, float>::value ? 0 : 1; }

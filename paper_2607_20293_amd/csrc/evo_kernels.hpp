@@ -37,9 +37,11 @@ struct KParams {
   const uint4* pk;           // packed projection matrices
   const LayerOff* loff;      // [L]
   const PackOff* poff;       // [L]
+  uint64_t pk_layers;        // fragment offset of layer 0 (layers are contiguous, each qkv, o, q, kv, o2, w1, w2)
   uint64_t pk_obs;           // fragment offset of W_obs (K padded to obs_pad)
   uint64_t pk_win;           // fp32 fragments of W_in (K = action_dim padded to 16)
   uint64_t pk_wout;          // fp32 fragments of W_out (rows padded to 16)
+  uint32_t raw_layers;       // float offset of layer 0 in raw
   uint32_t W_in, b_in, P_act, b_obs, P_mem, lnf_g, lnf_b, W_out, b_out, pad_;
   const float* tkv;          // [T][L][2d] time-token keys/values, indexed by timestep k
   const float* ddpm;         // [T][8] sampler constants by timestep k: sqrt(1-abar), 1/sqrt(abar), c0, ct, sigma
