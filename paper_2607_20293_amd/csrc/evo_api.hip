@@ -124,6 +124,7 @@ struct evo_policy {
   size_t cache_floats = 0;
   float* d_okv = nullptr;
   float* d_rpart = nullptr;  // per-query Eq. 6 terms [max_batch][3L][T]
+  float* d_rws = nullptr;    // partial Gram matrices of Eq. 6 (null where none are needed)
   // small-batch team variants: workgroups per one-sample tile, the largest
   // batch each serves and its per-member observation K/V stride, in the
   // order they are tried (smallest max_batch first); partial-residual
@@ -187,6 +188,7 @@ static void release(evo_policy* p) {
   (void)hipFree(p->d_cache);
   (void)hipFree(p->d_okv);
   (void)hipFree(p->d_rpart);
+  (void)hipFree(p->d_rws);
   (void)hipFree(p->d_xchg);
   (void)hipFree(p->d_tctr);
   (void)hipFree(p->d_derr);
@@ -444,6 +446,8 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
       CREATE_TRY(hipMalloc(&p->d_cache, p->cache_floats * s.cache_elt()));
       CREATE_TRY(hipMalloc(&p->d_okv, okv_floats * sizeof(float)));
       CREATE_TRY(hipMalloc(&p->d_rpart, (size_t)s.max_batch * U * T * sizeof(float)));
+      if (const size_t n = redundancy_workspace_floats(s.max_batch, U, T, (long long)s.H * d, p->n_cu))
+        CREATE_TRY(hipMalloc(&p->d_rws, n * sizeof(float)));
       if (!p->teams.empty()) {
         CREATE_TRY(hipMalloc(&p->d_xchg, xchg_rows * 3 * d * sizeof(float)));
         CREATE_TRY(hipMalloc(&p->d_tctr, ctr_tiles * 16 * sizeof(unsigned)));
@@ -803,7 +807,8 @@ int evo_redundancy_scores(evo_policy* p, int32_t rollouts, const float* acts, fl
     DeviceGuard guard(p->device);
     hipStream_t stream = (hipStream_t)hip_stream;
     if (p->launched && stream != p->last_stream) HIP_TRY(hipStreamWaitEvent(stream, p->ev_done, 0));
-    HIP_TRY(launch_redundancy(acts, rollouts, s.U(), s.T, (long long)s.H * s.d, p->d_rpart, scores_out, stream));
+    HIP_TRY(launch_redundancy(acts, rollouts, s.U(), s.T, (long long)s.H * s.d, p->n_cu, p->d_rws,
+                              p->d_rpart, scores_out, stream));
     HIP_TRY(hipEventRecord(p->ev_done, stream));
     p->last_stream = stream;
     p->launched = true;

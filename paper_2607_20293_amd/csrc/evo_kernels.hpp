@@ -111,9 +111,12 @@ int kernel_team_sizes(const KernelKey& key, int out[4]);
 
 // Eq. 6 dissimilarity scores from recorded activations acts [R][U][T][V]:
 // part [R][U][T] receives each query's term, d [U][T] their mean over R
-// (in query order).  T <= kGramMaxSteps.
+// (in query order).  T <= kGramMaxSteps, V a multiple of 32.  ws: partial
+// Gram matrices, redundancy_workspace_floats() floats for up to max_queries
+// queries on a device of n_cu CUs (may be null where that is 0).
 constexpr int kGramMaxSteps = 128;
-hipError_t launch_redundancy(const float* acts, int R, int U, int T, long long V, float* part, float* d,
-                             hipStream_t stream);
+size_t redundancy_workspace_floats(int max_queries, int U, int T, long long V, int n_cu);
+hipError_t launch_redundancy(const float* acts, int R, int U, int T, long long V, int n_cu, float* ws, float* part,
+                             float* d, hipStream_t stream);
 
 }  // namespace evo

@@ -112,3 +112,33 @@ def test_scores_and_guided_schedule_end_to_end():
     assert torch.isfinite(out).all()
     assert pol.stats()["refreshes_requested"] == 240 * R
     pol.close()
+
+
+@pytest.mark.parametrize("name,T,R", [("tiny", 2, 1), ("tiny", 16, 2), ("tiny", 17, 171), ("tiny", 128, 1),
+                                      ("pusht", 33, 1), ("pusht", 112, 2)])
+def test_scores_at_tile_edges(name, T, R):
+    """Step counts at the edges of the 16-step tiles (every tile count has its
+    own kernel), few and many queries (the elements split over workgroups, or
+    not), on activations that drift from step to step, against fp64.  A score
+    is a mean of cosines, each a sum of V products in chains of at most V / 4
+    fp32 additions, so it is within V / 4 * 2^-24 (plus rounding of the final
+    steps) of the exact value."""
+    import dataclasses
+    import torch
+    s = dataclasses.replace(I.TINY if name == "tiny" else I.PUSHT, n_steps=T)
+    U, V = 3 * s.n_layers, s.horizon * s.d_model
+    rng = np.random.default_rng([T, R])
+    acts = rng.standard_normal((R, U, 1, V), dtype=np.float32) + np.cumsum(
+        0.3 * rng.standard_normal((R, U, T, V), dtype=np.float32), axis=2, dtype=np.float32)
+    a = acts.astype(np.float64)
+    a /= np.sqrt((a * a).sum(-1, keepdims=True))
+    cos = a @ np.swapaxes(a, -1, -2)
+    want = ((T - 1 - (cos.sum(-1) - np.einsum("rutt->rut", cos))) / (T - 1)).mean(0)
+    pol = _policy(s, I.make_weights(s, 25), "fp32", R)
+    dev_acts = torch.from_numpy(acts).to(device())
+    got = pol.redundancy_scores(dev_acts).cpu().numpy()
+    err, tol = float(np.max(np.abs(got - want))), V / 4 * 2.0 ** -24 + 1e-6
+    say(f"[gpu] scores {name} T={T} R={R}: max-abs {err:.3e} (tol {tol:.1e})")
+    assert err <= tol
+    assert np.array_equal(got, pol.redundancy_scores(dev_acts).cpu().numpy())  # fixed order of every sum
+    pol.close()
