@@ -41,6 +41,7 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;
 constexpr int kTargetWG = 512;      // split K below this many output tiles
@@ -342,6 +343,12 @@ __global__ void __launch_bounds__(kThreads) conv_kernel(const ConvArgs a) {
     }
 }
 
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x2 round4(f32x4 v) {  // four bf16, round to nearest even
+  const bf16x2_t lo = {(__bf16)v[0], (__bf16)v[1]}, hi = {(__bf16)v[2], (__bf16)v[3]};
+  return u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+}
+
 enum { GN_PLAIN = 0, GN_MAXPOOL = 1, GN_AVGPOOL = 2 };
 
 struct GnArgs {
@@ -353,6 +360,7 @@ struct GnArgs {
   const float* beta;
   const float* res;  // residual [N][HW][C] or NULL
   float* y;          // PLAIN: [N][HW][C] (may be x); MAXPOOL: [N][Hp][Wp][C]; AVGPOOL: out + n * out_stride
+  __bf16* yb;        // MAXPOOL: a rounded copy of y, or NULL
   double2* part;     // [N][groups][ps_stats] shifted (sum, sum of squares)
   float* shift;      // [N][groups] the shift x0 (read before the apply pass may overwrite x in place)
   int relu, mode, H, W, C, G, gpw, ps_stats, ps_apply, Hp, Wp, out_stride;
@@ -524,7 +532,9 @@ __global__ void __launch_bounds__(kThreads) gn_apply_kernel(const GnArgs a) {
           for (int k = 0; k < 4; ++k) m[k] = fmaxf(m[k], r[k]);
         }
       }
-      *reinterpret_cast<f32x4*>(a.y + (size_t)n * HWp * a.C + (size_t)p * a.C + c) = m;
+      const size_t o = (size_t)n * HWp * a.C + (size_t)p * a.C + c;
+      *reinterpret_cast<f32x4*>(a.y + o) = m;
+      if (a.yb) *reinterpret_cast<u32x2*>(a.yb + o) = round4(m);
     }
   } else {
     // global average pooling (one pixel chunk): column sums over the rows
@@ -663,7 +673,9 @@ __global__ void __launch_bounds__(kThreads) gn_fused_kernel(const GnArgs a) {
           for (int k = 0; k < 4; ++k) m[k] = fmaxf(m[k], r[k]);
         }
       }
-      *reinterpret_cast<f32x4*>(a.y + (size_t)n * HWp * a.C + (size_t)p * a.C + c) = m;
+      const size_t o = (size_t)n * HWp * a.C + (size_t)p * a.C + c;
+      *reinterpret_cast<f32x4*>(a.y + o) = m;
+      if (a.yb) *reinterpret_cast<u32x2*>(a.yb + o) = round4(m);
     }
   } else {
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -689,6 +701,559 @@ __global__ void __launch_bounds__(kThreads) gn_fused_kernel(const GnArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- fused layers
+// Convolution + GroupNorm + shortcut + ReLU (+ global average pooling) of
+// whole images in one kernel (bf16 operands, groups of 16 channels, 3x3 or
+// 1x1, channel counts multiples of 64, maps that fit a workgroup).
+//
+// A workgroup takes `ipw` whole images and 16 * NBW * WN output channels, so
+// that every GroupNorm group it produces is complete and the conv output
+// never travels through memory.  Its input pixels, 64 channels at a time,
+// sit in LDS as zero-bordered images (a row of W + 1 pixels: the zero column
+// ends one row and begins the next), so the nine taps of a 3x3 kernel read
+// the same LDS bytes at nine offsets instead of being gathered nine times.
+// The stride of a pixel is 144 bytes (128 + 16), which spreads 16 consecutive
+// pixels over all LDS banks.  Weights come straight from L2 as packed MFMA
+// fragments, D k-steps ahead in registers.  Products are transposed (weights
+// first), so a lane holds four channels of one pixel: a 16-channel group is
+// one accumulator block, and its sums are in-lane adds and two lane swaps.
+//
+// Waves: WM along the pixels, WN along the channels, WK along K (each its
+// share of the 64-channel chunks; partial sums meet in LDS).  What bounds a
+// large layer: matrix cores (16 cycles a 16x16x32 MFMA) against 1 KiB of LDS
+// per pixel block and 1 KiB of L2 per channel block and k-step; a wave tile
+// of 7 x 4 or 8 x 4 blocks needs about half of either.  A small batch takes
+// 16 channels a workgroup, for more workgroups and a shorter weight stream.
+// An image's results do not depend on its place in a tile, the other images
+// or the batch: rows of a product are independent and the statistics sum a
+// row's channels, then the rows of the image, in a fixed order.
+constexpr int kPix = 144;  // LDS bytes of a pixel's 64 channels
+
+struct FusedArgs {
+  const __bf16* x;      // [N][H][W][Cin]
+  const uint4* w;       // fragments [Cin / 64][taps][2][Cout / 16][64 lanes]
+  const float* gamma;
+  const float* beta;
+  const float* res;     // shortcut [N][Ho][Wo][Cout] or NULL
+  float* yf;            // fp32 output or NULL
+  __bf16* yb;           // bf16 output (rounded) or NULL
+  float* feat;          // mean over the pixels, row n at feat + n * out_stride, or NULL
+  int out_stride, relu;
+  int N, H, W, Ho, Wo, Cin, Cout, stride;
+  int ipw, PW, PP, nit;  // images per workgroup, LDS row and image pixels, chunks per K share
+  uint32_t div_px, div_pw, div_hw, div_wo, div_ipw;  // ceil(2^32 / d) of PP, PW, Ho * Wo, Wo, ipw (0: ipw is 1)
+  int mt, nt, a_bytes;
+  float eps;
+};
+
+__device__ __forceinline__ int fast_div(int n, uint32_t m) { return (int)__umulhi((uint32_t)n, m); }
+
+__device__ __forceinline__ float row16_sum(float v) {  // over the lanes that share lane / 16
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, true));
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, true));
+  return v;
+}
+__device__ __forceinline__ float quad_sum(float v) {  // over the lanes that share lane % 16
+  u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// (The statistics follow the A region in LDS: one image, the waves' sums,
+// twice; several, row sums [channel blocks][rows], mean and 1 / deviation.)
+template <int MBW, int NBW, int WM, int WN, int WK, int TAPS>
+__global__ void __launch_bounds__(WM * WN * WK * 64, MBW * NBW > 32 ? 1 : 2) conv_gn_kernel(const FusedArgs a) {
+  constexpr int NT = WM * WN * WK * 64, NB = NBW * WN, S = TAPS * 2;
+  constexpr int D = TAPS == 1 ? 2 : NBW == 4 ? 3 : NBW == 2 ? 6 : 9;  // k-steps of weights in flight
+  static_assert(S % D == 0, "ring");
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lc = lane & 15, lq = lane >> 4;
+  const int kg = wave / (WM * WN), wm = wave % (WM * WN) / WN, wn = wave % WN;
+  const int id = xcd_linear(blockIdx.x, a.mt * a.nt), nti = id % a.nt, img0 = id / a.nt * a.ipw;
+  const int HW = a.Ho * a.Wo, rows = a.ipw * HW, nbt = a.Cout / 16, nb0 = nti * NB + wn * NBW;
+
+  // ---- weights: the wave's k-steps are consecutive in memory
+  const int steps = a.nit * S, ks0 = kg * steps;
+  const auto wrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(a.w), (short)0, a.Cin / 64 * S * nbt * 1024, 0x00020000);
+  const auto wload = [&](int j, int n) {
+    return __builtin_bit_cast(
+        uint4, __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16, ((ks0 + min(j, steps - 1)) * nbt + nb0 + n) * 1024, 0));
+  };
+  uint4 ring[D][NBW];
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) ring[d][n] = wload(d, n);
+
+  // LDS byte of tap (0, 0), channel octet lq, of this lane's output pixels
+  int abase[MBW];
+#pragma unroll
+  for (int m = 0; m < MBW; ++m) {
+    const int r = (wm * MBW + m) * 16 + lc;
+    int px = 0;
+    if (r < rows) {
+      const int im = fast_div(r, a.div_hw), q = r - im * HW;
+      if (TAPS == 1) {
+        px = r;
+      } else {
+        const int oy = fast_div(q, a.div_wo), ox = q - oy * a.Wo;
+        px = im * a.PP + oy * a.stride * a.PW + ox * a.stride;
+      }
+    }
+    abase[m] = (kg * a.ipw * a.PP + px) * kPix + lq * 16;
+  }
+
+  f32x4 acc[MBW][NBW];
+#pragma unroll
+  for (int m = 0; m < MBW; ++m)
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int it = 0; it < a.nit; ++it) {
+    // stage 64 channels of every K share's images (1x1: of the pixels used),
+    // U 16-byte loads a thread in flight
+    const int units = WK * a.ipw * a.PP * 8;
+    constexpr int U = 8;
+    for (int u0 = tid; u0 < units; u0 += U * NT) {
+      uint4 v[U];
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        const int u = u0 + q * NT, oct = u & 7, slot = u >> 3, gi = fast_div(slot, a.div_px), px = slot - gi * a.PP;
+        const int g = a.div_ipw ? fast_div(gi, a.div_ipw) : gi, im = gi - g * a.ipw, img = img0 + im;
+        int iy, ix;
+        if (TAPS == 1) {
+          const int oy = fast_div(px, a.div_wo);
+          iy = oy * a.stride;
+          ix = (px - oy * a.Wo) * a.stride;
+        } else {
+          const int py = fast_div(px, a.div_pw);
+          iy = py - 1;
+          ix = px - py * a.PW - 1;
+        }
+        v[q] = make_uint4(0u, 0u, 0u, 0u);
+        if (u < units && img < a.N && iy >= 0 && iy < a.H && ix >= 0)
+          v[q] = *reinterpret_cast<const uint4*>(a.x + (((size_t)img * a.H + iy) * a.W + ix) * a.Cin + (g * a.nit + it) * 64 + oct * 8);
+      }
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        const int u = u0 + q * NT;
+        if (u < units) *reinterpret_cast<uint4*>(lds + (u >> 3) * kPix + (u & 7) * 16) = v[q];
+      }
+    }
+    __syncthreads();
+    uint4 af[2][MBW];
+    const auto aload = [&](int s, uint4 (&f)[MBW]) {
+      const int tap = s >> 1, off = (TAPS == 1 ? 0 : (tap / 3 * a.PW + tap % 3) * kPix) + (s & 1) * 64;
+#pragma unroll
+      for (int m = 0; m < MBW; ++m) f[m] = *reinterpret_cast<const uint4*>(lds + abase[m] + off);
+    };
+    aload(0, af[0]);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if (s + 1 < S) aload(s + 1, af[(s + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < MBW; ++m)
+#pragma unroll
+        for (int n = 0; n < NBW; ++n)
+          acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ring[s % D][n]),
+                                                              __builtin_bit_cast(bf16x8_t, af[s & 1][m]), acc[m][n], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int n = 0; n < NBW; ++n) ring[s % D][n] = wload(it * S + s + D, n);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();  // the region is rewritten by the next chunk, or by what follows
+  }
+
+  // ---- K shares: row block m is summed, in share order, by share
+  // m * WK / MBW, which also finishes it
+  const auto mine = [&](int m) { return WK == 1 || m * WK / MBW == kg; };
+  if constexpr (WK > 1) {
+    f32x4* part = reinterpret_cast<f32x4*>(lds);
+    // slot of share g's contribution to a block that another share owns
+    const auto at = [&](int g, int m, int n) {
+      const int x = g - (g > m * WK / MBW ? 1 : 0);
+      return (((x * WM * WN + wm * WN + wn) * MBW + m) * NBW + n) * 64 + lane;
+    };
+#pragma unroll
+    for (int m = 0; m < MBW; ++m)
+      if (!mine(m)) {
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) part[at(kg, m, n)] = acc[m][n];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < MBW; ++m)
+      if (mine(m)) {
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) {
+          f32x4 t = kg == 0 ? acc[m][n] : part[at(0, m, n)];
+#pragma unroll
+          for (int g = 1; g < WK; ++g) t += g == kg ? acc[m][n] : part[at(g, m, n)];
+          acc[m][n] = t;
+        }
+      }
+    __syncthreads();
+  }
+
+  // ---- GroupNorm statistics of every image and group (mean, then the
+  // squares around it).  One image a workgroup: a lane's rows, the wave's
+  // lanes, then the waves in order.  Several: the channels of each row to
+  // LDS, then the rows of an image.
+  float* const rsum = reinterpret_cast<float*>(lds + a.a_bytes);
+  const double inv_cnt = 1.0 / ((double)HW * 16.0);
+  const auto row_of = [&](int m) { return (wm * MBW + m) * 16 + lc; };
+  float mu[NBW], rs[NBW];  // one image; several: in LDS
+  float* const smean = rsum + NB * rows;  // [NB][ipw]
+  float* const srstd = smean + NB * a.ipw;
+  int im[MBW];
+#pragma unroll
+  for (int m = 0; m < MBW; ++m) im[m] = a.ipw > 1 ? fast_div(min(row_of(m), rows - 1), a.div_hw) : 0;
+  if (a.ipw == 1) {
+    constexpr int NW = WM * WK;
+    const auto total = [&](float* buf, auto value, double (&out)[NBW]) {  // buf [NW][NB]
+#pragma unroll
+      for (int n = 0; n < NBW; ++n) {
+        float t = 0.f;
+#pragma unroll
+        for (int m = 0; m < MBW; ++m)
+          if (mine(m)) {
+            const float v = value(m, n);
+            t += row_of(m) < rows ? v : 0.f;
+          }
+        t = quad_sum(row16_sum(t));
+        if (lane == 0) buf[(kg * WM + wm) * NB + wn * NBW + n] = t;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int n = 0; n < NBW; ++n) {
+        double t = 0.0;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) t += (double)buf[x * NB + wn * NBW + n];
+        out[n] = t;
+      }
+    };
+    double t[NBW];
+    total(rsum, [&](int m, int n) { return (acc[m][n][0] + acc[m][n][1]) + (acc[m][n][2] + acc[m][n][3]); }, t);
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) mu[n] = (float)(t[n] * inv_cnt);
+    total(rsum + NW * NB, [&](int m, int n) {
+      const f32x4 d = acc[m][n] - mu[n];
+      return (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
+    }, t);
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) rs[n] = (float)(1.0 / std::sqrt(t[n] * inv_cnt + (double)a.eps));
+  } else {
+    const int pairs = NB * a.ipw;
+    int tp = 64;                         // threads per (group, image): rows l, l + tp, ..., then a tree
+    while (tp > 1 && tp * pairs > NT) tp >>= 1;
+    const auto total = [&](auto value, auto finish, float* st) {
+#pragma unroll
+      for (int m = 0; m < MBW; ++m)
+        if (mine(m)) {
+          float v[NBW];
+#pragma unroll
+          for (int n = 0; n < NBW; ++n) v[n] = quad_sum(value(m, n));
+          if (lq == 0 && row_of(m) < rows) {
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) rsum[(wn * NBW + n) * rows + row_of(m)] = v[n];
+          }
+        }
+      __syncthreads();
+      for (int p0 = 0; p0 < pairs; p0 += NT / tp) {
+        const int p = p0 + tid / tp, l = tid % tp, nb = fast_div(p, a.div_ipw);
+        double sum = 0.0;
+        if (p < pairs) {
+          const float* src = rsum + nb * rows + (p - nb * a.ipw) * HW;
+          for (int r = l; r < HW; r += tp) sum += (double)src[r];
+        }
+        for (int h = tp >> 1; h > 0; h >>= 1) sum += __shfl_xor(sum, h);
+        if (p < pairs && l == 0) st[p] = finish(sum);
+      }
+      __syncthreads();
+    };
+    total([&](int m, int n) { return (acc[m][n][0] + acc[m][n][1]) + (acc[m][n][2] + acc[m][n][3]); },
+          [&](double t) { return (float)(t * inv_cnt); }, smean);
+    total([&](int m, int n) {
+      const f32x4 d = acc[m][n] - smean[(wn * NBW + n) * a.ipw + im[m]];
+      return (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
+    }, [&](double t) { return (float)(1.0 / std::sqrt(t * inv_cnt + (double)a.eps)); }, srstd);
+  }
+
+  // ---- normalise, add the shortcut, ReLU, store
+  float* const fin = reinterpret_cast<float*>(lds);  // [rows][16 NB] (average pooling)
+  {
+    f32x4 gm[NBW], bt[NBW];
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) {
+      const int ch = (nb0 + n) * 16 + lq * 4;
+      gm[n] = *reinterpret_cast<const f32x4*>(a.gamma + ch);
+      bt[n] = *reinterpret_cast<const f32x4*>(a.beta + ch);
+    }
+    const auto live = [&](int m) { return row_of(m) < rows && img0 + im[m] < a.N; };
+    const auto at = [&](int m) { return ((size_t)img0 * HW + row_of(m)) * a.Cout + nb0 * 16 + lq * 4; };
+    // the shortcut's rows one block ahead (an output may overwrite it in place,
+    // each element after its own read)
+    f32x4 res[2][NBW];
+    const auto rload = [&](int m, f32x4 (&v)[NBW]) {
+#pragma unroll
+      for (int n = 0; n < NBW; ++n) {
+        v[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (a.res && mine(m) && live(m)) v[n] = *reinterpret_cast<const f32x4*>(a.res + at(m) + n * 16);
+      }
+    };
+    rload(0, res[0]);
+#pragma unroll
+    for (int m = 0; m < MBW; ++m) {
+      if (m + 1 < MBW) rload(m + 1, res[(m + 1) & 1]);
+      if (!mine(m) || !live(m)) continue;
+      const size_t o = at(m);
+#pragma unroll
+      for (int n = 0; n < NBW; ++n) {
+        const int q = (wn * NBW + n) * a.ipw + im[m];
+        const float mn = a.ipw == 1 ? mu[n] : smean[q], rd = a.ipw == 1 ? rs[n] : srstd[q];
+        f32x4 v = (acc[m][n] - mn) * rd * gm[n] + bt[n];
+        if (a.res) v += res[m & 1][n];
+        if (a.relu) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+        }
+        if (a.yf) *reinterpret_cast<f32x4*>(a.yf + o + n * 16) = v;
+        if (a.yb) *reinterpret_cast<u32x2*>(a.yb + o + n * 16) = round4(v);
+        if (a.feat) *reinterpret_cast<f32x4*>(fin + (size_t)row_of(m) * (16 * NB) + (wn * NBW + n) * 16 + lq * 4) = v;
+      }
+    }
+  }
+  if (a.feat) {
+    __syncthreads();
+    for (int i = tid; i < a.ipw * 16 * NB; i += NT) {
+      const int g = i / (16 * NB), c = i % (16 * NB);
+      if (img0 + g >= a.N) break;
+      float s = 0.f;
+      for (int r = 0; r < HW; ++r) s += fin[(size_t)(g * HW + r) * (16 * NB) + c];
+      a.feat[(size_t)(img0 + g) * a.out_stride + nti * (16 * NB) + c] = s / (float)HW;
+    }
+  }
+}
+
+// weights [Cout][k][k][Cin] fp32 -> bf16 fragments of conv_gn_kernel
+__global__ void pack_fused_kernel(const float* __restrict__ w, int Cout, int Cin, int taps, uint4* dst) {
+  const long long total = (long long)Cin / 32 * taps * (Cout / 16) * 64;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
+    const int lane = (int)(i % 64);
+    const long long f = i / 64;
+    const int nb = (int)(f % (Cout / 16)), s = (int)(f / (Cout / 16));
+    const int h = s & 1, tap = (s >> 1) % taps, chunk = (s >> 1) / taps;
+    const int o = nb * 16 + (lane & 15), c = chunk * 64 + h * 32 + (lane >> 4) * 8;
+    bf16x8_t v;
+    for (int e = 0; e < 8; ++e) v[e] = (__bf16)w[((size_t)o * taps + tap) * Cin + c + e];
+    dst[i] = __builtin_bit_cast(uint4, v);
+  }
+}
+
+// compiled wave arrangements (MBW, NBW, WM, WN, WK)
+#define EVO_FUSED(X)                                                                              \
+  X(7, 4, 4, 1, 1) X(9, 4, 4, 1, 1) X(4, 4, 2, 2, 1) X(8, 4, 1, 2, 2) X(9, 4, 1, 2, 2)            \
+  X(5, 4, 1, 2, 2) X(5, 4, 1, 1, 4) X(4, 1, 8, 1, 1) X(5, 1, 8, 1, 1) X(2, 1, 4, 1, 2)            \
+  X(3, 1, 4, 1, 2) X(2, 1, 4, 1, 1) X(3, 1, 4, 1, 1) X(3, 1, 1, 1, 4) X(3, 1, 1, 1, 2)            \
+  X(1, 1, 1, 1, 8) X(1, 1, 1, 1, 4) X(3, 2, 1, 2, 4) X(3, 2, 1, 2, 2) X(5, 2, 1, 2, 2)
+
+struct FusedCfg {
+  int mbw, nbw, wm, wn, wk;
+};
+constexpr FusedCfg kFused[] = {
+#define X(a, b, c, d, e) {a, b, c, d, e},
+    EVO_FUSED(X)
+#undef X
+};
+constexpr size_t kLdsBytes = 160 * 1024;
+
+// ---------------------------------------------------------------- fused stem
+// 7x7 stride-2 convolution (at most 4 image channels), GroupNorm (groups of
+// 16), ReLU and 3x3 stride-2 max pooling of one image's 16 * NB channels in
+// one kernel: the conv output (231 MB for 512 frames of 84x84, read three
+// times when it went through memory) is formed twice from the image in LDS
+// instead, once for the statistics and once, four rows at a time, to be
+// normalised and pooled.
+//
+// The image sits in LDS in bf16 with 4 channels a pixel (8 bytes) and its
+// zero border, so a kernel row of 7 pixels plus one of weight zero is one
+// K step of 32, and an operand fragment is an aligned 16-byte read at pixel
+// 2 ow + 2 (lane / 16) of the row.  The 7 x NB weight fragments stay in
+// registers.  512 frames of 84x84: three kernels 282 us, this one STEM_NOW.
+constexpr int kStemWaves = 8, kStripRows = 5;
+
+struct StemArgs {
+  const float* x;    // [N][H][W][Cin]
+  const uint4* w;    // fragments [7][C / 16][64 lanes]
+  const float* gamma;
+  const float* beta;
+  float* yf;         // [N][Hp][Wp][C]
+  __bf16* yb;        // the same rounded
+  int H, W, Cin, Ho, Wo, Hp, Wp, C, PW, PR, nt;  // PW, PR: pixels a row and rows of the bordered image
+  uint32_t div_pw, div_wo, div_wp;
+  int strip_off, red_off;  // LDS bytes
+  float eps;
+};
+
+template <int NB>
+__global__ void __launch_bounds__(kStemWaves * 64) stem_kernel(const StemArgs a) {
+  constexpr int NT = kStemWaves * 64, LD = 16 * NB + 4;  // strip floats a pixel (padded: no bank conflicts)
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  float* const strip = reinterpret_cast<float*>(lds + a.strip_off);      // [kStripRows][Wo][LD]
+  double2* const red = reinterpret_cast<double2*>(lds + a.red_off);      // [waves][NB]
+  const int tid = threadIdx.x, lane = tid & 63, lc = lane & 15, lq = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int img = blockIdx.x / a.nt, nb0 = blockIdx.x % a.nt * NB, nbt = a.C / 16;
+
+  uint4 wf[7][NB];
+#pragma unroll
+  for (int k = 0; k < 7; ++k)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) wf[k][n] = a.w[(size_t)(k * nbt + nb0 + n) * 64 + lane];
+
+  const float* src = a.x + (size_t)img * a.H * a.W * a.Cin;
+  constexpr int U = 6;  // pixels in flight a thread
+  for (int p0 = tid; p0 < a.PR * a.PW; p0 += U * NT) {
+    f32x4 v[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int p = p0 + q * NT, py = fast_div(p, a.div_pw), iy = py - 3, ix = p - py * a.PW - 3;
+      v[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (p < a.PR * a.PW && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (c < a.Cin) v[q][c] = src[(iy * a.W + ix) * a.Cin + c];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (p0 + q * NT < a.PR * a.PW) *reinterpret_cast<u32x2*>(lds + (p0 + q * NT) * 8) = round4(v[q]);
+  }
+  __syncthreads();
+
+  // conv outputs of pixels px0 + lc (clamped to the last), channels 4 lq .. + 3 of each block
+  const int HW = a.Ho * a.Wo;
+  const auto conv = [&](int px0, f32x4 (&y)[NB]) {
+    const int r = min(px0 + lc, HW - 1), oh = fast_div(r, a.div_wo), ow = r - oh * a.Wo;
+    const unsigned char* at = lds + (2 * oh * a.PW + 2 * ow) * 8 + lq * 16;
+    uint4 f[7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) f[k] = *reinterpret_cast<const uint4*>(at + k * a.PW * 8);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) y[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 7; ++k)
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+        y[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf[k][n]), __builtin_bit_cast(bf16x8_t, f[k]),
+                                                      y[n], 0, 0, 0);
+  };
+
+  // ---- statistics: sums of (x - x0), x0 the group's first element, fp32 in
+  // a lane, fp64 across the waves in order
+  f32x4 y[NB];
+  float x0[NB], s[NB], q[NB];
+  conv(0, y);
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    x0[n] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(y[n][0])));
+    s[n] = q[n] = 0.f;
+  }
+  for (int b = w * 16; b < HW; b += kStemWaves * 16) {
+    conv(b, y);
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      const f32x4 d = y[n] - x0[n];
+      const float ds = (d[0] + d[1]) + (d[2] + d[3]), dq = (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
+      s[n] += b + lc < HW ? ds : 0.f;
+      q[n] += b + lc < HW ? dq : 0.f;
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const float ts = quad_sum(row16_sum(s[n])), tq = quad_sum(row16_sum(q[n]));
+    if (lane == 0) red[w * NB + n] = make_double2((double)ts, (double)tq);
+  }
+  __syncthreads();
+  float mean[NB], rstd[NB];
+  f32x4 gm[NB], bt[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    double S = 0.0, Q = 0.0;
+#pragma unroll
+    for (int x = 0; x < kStemWaves; ++x) {
+      S += red[x * NB + n].x;
+      Q += red[x * NB + n].y;
+    }
+    const double cnt = (double)HW * 16.0, m = S / cnt, var = std::max(Q / cnt - m * m, 0.0);
+    mean[n] = (float)((double)x0[n] + m);
+    rstd[n] = (float)(1.0 / std::sqrt(var + (double)a.eps));
+    gm[n] = *reinterpret_cast<const f32x4*>(a.gamma + (nb0 + n) * 16 + lq * 4);
+    bt[n] = *reinterpret_cast<const f32x4*>(a.beta + (nb0 + n) * 16 + lq * 4);
+  }
+
+  // ---- four conv rows at a time, kept in a ring of five: normalise, ReLU,
+  // then the two pooled rows they complete (pooled row p covers conv rows
+  // 2 p - 1 .. 2 p + 1)
+  for (int c0 = 0; c0 < a.Ho; c0 += 4) {
+    const int c1 = min(a.Ho, c0 + 4), end = c1 * a.Wo;
+    for (int b = c0 * a.Wo + w * 16; b < end; b += kStemWaves * 16) {
+      conv(b, y);
+      const int r = b + lc, oh = fast_div(r, a.div_wo), ow = r - oh * a.Wo;
+      if (r < end) {
+        float* dst = strip + (oh % kStripRows * a.Wo + ow) * LD + lq * 4;
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+          f32x4 v = (y[n] - mean[n]) * rstd[n] * gm[n] + bt[n];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+          *reinterpret_cast<f32x4*>(dst + n * 16) = v;
+        }
+      }
+    }
+    __syncthreads();
+    const int p0 = c0 / 2, p1 = c1 == a.Ho ? a.Hp : c1 / 2;
+    for (int i = tid; i < (p1 - p0) * a.Wp * 4 * NB; i += NT) {
+      const int c4 = i % (4 * NB), px = i / (4 * NB), pr = fast_div(px, a.div_wp), pw = px - pr * a.Wp, ph = p0 + pr;
+      f32x4 m = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+      for (int u = -1; u <= 1; ++u)
+#pragma unroll
+        for (int v = -1; v <= 1; ++v) {
+          const int ih = 2 * ph + u, iw = 2 * pw + v;
+          if (ih < 0 || ih >= a.Ho || iw < 0 || iw >= a.Wo) continue;
+          const f32x4 t = *reinterpret_cast<const f32x4*>(strip + (ih % kStripRows * a.Wo + iw) * LD + c4 * 4);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) m[k] = fmaxf(m[k], t[k]);
+        }
+      const size_t o = (((size_t)img * a.Hp + ph) * a.Wp + pw) * a.C + nb0 * 16 + c4 * 4;
+      *reinterpret_cast<f32x4*>(a.yf + o) = m;
+      *reinterpret_cast<u32x2*>(a.yb + o) = round4(m);
+    }
+    __syncthreads();
+  }
+}
+
+// stem weights [C][7][7][Cin] fp32 -> bf16 fragments of stem_kernel
+__global__ void pack_stem_kernel(const float* __restrict__ w, int C, int Cin, uint4* dst) {
+  const int total = 7 * (C / 16) * 64;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+    const int lane = i % 64, nb = i / 64 % (C / 16), ky = i / 64 / (C / 16), o = nb * 16 + (lane & 15);
+    bf16x8_t v;
+    for (int e = 0; e < 8; ++e) {
+      const int kx = 2 * (lane >> 4) + e / 4, c = e % 4;
+      v[e] = (__bf16)(kx < 7 && c < Cin ? w[((size_t)(o * 7 + ky) * 7 + kx) * Cin + c] : 0.f);
+    }
+    dst[i] = __builtin_bit_cast(uint4, v);
+  }
+}
+
 // weights [Cout][K] fp32 -> [Cout][Kp] operand type, zero padded
 __global__ void pack_conv_kernel(const float* __restrict__ w, int Cout, int K, int Kp, int bf, void* dst) {
   const long long total = (long long)Cout * Kp;
@@ -702,9 +1267,15 @@ __global__ void pack_conv_kernel(const float* __restrict__ w, int Cout, int K, i
 
 unsigned grid_for(long long total) { return (unsigned)std::min<long long>((total + 255) / 256, 16384); }
 
+// A fused layer's launch, chosen at creation for the encoder's max_batch.
+struct FusedPlan {
+  int cfg = -1, ipw = 0, PW = 0, PP = 0, nit = 0, a_bytes = 0, lds = 0;
+};
+
 struct ConvLayer {
   int cin, cout, k, stride, pad, K, Kp;
   void* w = nullptr;             // packed operand weights
+  FusedPlan fp;
   const float* gamma = nullptr;  // GroupNorm affine (device, inside the raw copy)
   const float* beta = nullptr;
 };
@@ -715,6 +1286,8 @@ struct evo_encoder {
   evo_encoder_desc desc{};
   int device = 0;
   int bf = 1;
+  bool fused = false;            // the layers after the stem run as conv_gn_kernel
+  int stem_nb = 0;               // 16-channel blocks a workgroup of stem_kernel takes (0: the stem runs unfused)
   float* d_raw = nullptr;        // fp32 parameter copy (GroupNorm affine, packing source)
   std::vector<ConvLayer> convs;  // stem, then per block a, b[, d]
   float* buf[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -794,6 +1367,145 @@ ConvPlan plan_conv(int M, int Cout, int steps) {
   pl.spp = cdiv(steps, splits);
   pl.splits = cdiv(steps, pl.spp);  // every split has at least one step
   return pl;
+}
+
+// Cheapest wave arrangement of a fused layer on an H x W input.  Cycles of a
+// workgroup: matrix cores, its weight stream from L2 (48 bytes a cycle and
+// CU), its LDS reads, each shared by the workgroups that run on a CU at once;
+// plus staging and about 5000 for its start and statistics.
+bool plan_fused(int max_batch, const ConvLayer& L, int H, int W, bool pool, int n_cu, FusedPlan* out) {
+  const int Ho = out_size(H, L.k, L.stride, L.pad), Wo = out_size(W, L.k, L.stride, L.pad), HW = Ho * Wo;
+  if ((L.k != 3 && L.k != 1) || L.cin % 64 || L.cout % 64 || Wo < 2 || HW < 2) return false;
+  const int nch = L.cin / 64, S = L.k * L.k * 2;
+  const int PW = L.k == 1 ? Wo : W + 1, PP = L.k == 1 ? HW : (H + 2) * PW + 1;
+  double best = 0.0;
+  out->cfg = -1;
+  for (int c = 0; c < (int)(sizeof(kFused) / sizeof(kFused[0])); ++c) {
+    const FusedCfg& f = kFused[c];
+    const int nb = f.nbw * f.wn, cap = 16 * f.mbw * f.wm, waves = f.wm * f.wn * f.wk;
+    if (L.cout % (16 * nb) || nch % f.wk || cap < HW) continue;
+    for (int ipw = 1; ipw <= std::min(cap / HW, max_batch); ++ipw) {
+      const int rows = ipw * HW;
+      const long long stage = (long long)f.wk * ipw * PP * kPix;
+      const long long part = (long long)(f.wk - 1) * f.wm * f.wn * f.mbw * f.nbw * 1024;
+      const long long a_bytes = (std::max({stage, part, pool ? (long long)rows * 16 * nb * 4 : 0ll}) + 15) / 16 * 16;
+      const long long lds = a_bytes + (ipw == 1 ? 2ll * f.wm * f.wk * nb * 4 : (long long)nb * (rows + 2 * ipw) * 4);
+      if (lds > (long long)kLdsBytes) continue;
+      const int nit = nch / f.wk;
+      const long long wgs = (long long)cdiv(max_batch, ipw) * (L.cout / (16 * nb));
+      const long long occ = std::max(1ll, std::min((long long)kLdsBytes / lds, 8ll / waves));
+      const double on = (double)std::min<long long>(occ, (wgs + n_cu - 1) / n_cu);  // workgroups that share a CU
+      const double steps = (double)nit * S, one = f.mbw * f.nbw * 16.0 * steps;      // one wave's MFMAs
+      const double mf = std::max(one * waves * on / 4.0, one), l2 = 16.0 * nb * f.wm * L.K * 2 / 48.0 * on;
+      const double ld = waves * steps * f.mbw * 8.0 * on, st = stage / 32.0 * nit * on;
+      const double cost = (double)((wgs + n_cu * occ - 1) / (n_cu * occ)) * (std::max({mf, l2, ld}) + st + 5000.0);
+      if (out->cfg < 0 || cost < best) {
+        best = cost;
+        *out = FusedPlan{c, ipw, PW, PP, nit, (int)a_bytes, (int)lds};
+      }
+    }
+  }
+  return out->cfg >= 0;
+}
+
+const void* fused_kernel(int cfg, int k) {
+  int i = 0;
+#define X(a, b, c, d, e)                                                                            \
+  if (cfg == i++)                                                                                   \
+    return k == 1 ? reinterpret_cast<const void*>(&conv_gn_kernel<a, b, c, d, e, 1>)                \
+                  : reinterpret_cast<const void*>(&conv_gn_kernel<a, b, c, d, e, 9>);
+  EVO_FUSED(X)
+#undef X
+  return nullptr;
+}
+
+// One fused layer on N images of H x W (`*Ho` x `*Wo` out).
+hipError_t launch_fused(const ConvLayer& L, const __bf16* x, int N, int H, int W, int* Ho, int* Wo, const float* res,
+                        int relu, float* yf, __bf16* yb, float* feat, int out_stride, hipStream_t st) {
+  const FusedPlan& p = L.fp;
+  const FusedCfg& f = kFused[p.cfg];
+  const auto magic = [](int d) { return (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); };
+  FusedArgs a;
+  a.x = x;
+  a.w = reinterpret_cast<const uint4*>(L.w);
+  a.gamma = L.gamma;
+  a.beta = L.beta;
+  a.res = res;
+  a.yf = yf;
+  a.yb = yb;
+  a.feat = feat;
+  a.out_stride = out_stride;
+  a.relu = relu;
+  a.N = N;
+  a.H = H;
+  a.W = W;
+  a.Ho = *Ho = out_size(H, L.k, L.stride, L.pad);
+  a.Wo = *Wo = out_size(W, L.k, L.stride, L.pad);
+  a.Cin = L.cin;
+  a.Cout = L.cout;
+  a.stride = L.stride;
+  a.ipw = p.ipw;
+  a.PW = p.PW;
+  a.PP = p.PP;
+  a.nit = p.nit;
+  a.div_px = magic(p.PP);
+  a.div_pw = magic(p.PW);
+  a.div_hw = magic(a.Ho * a.Wo);
+  a.div_wo = magic(a.Wo);
+  a.div_ipw = p.ipw > 1 ? magic(p.ipw) : 0u;
+  a.mt = cdiv(N, p.ipw);
+  a.nt = L.cout / (16 * f.nbw * f.wn);
+  a.a_bytes = p.a_bytes;
+  a.eps = 1e-5f;
+  void* args[] = {&a};
+  return hipLaunchKernel(fused_kernel(p.cfg, L.k), dim3((unsigned)(a.mt * a.nt)), dim3(f.wm * f.wn * f.wk * 64), args,
+                         (size_t)p.lds, st);
+}
+
+int stem_pitch(int W) { return (W + 8) / 2 * 2; }
+int stem_lds(const evo_encoder_desc& d, int nb, int* strip_off, int* red_off) {
+  const int Ho = out_size(d.height, 7, 2, 3), Wo = out_size(d.width, 7, 2, 3);
+  const long long img = ((long long)(2 * (Ho - 1) + 7) * stem_pitch(d.width) * 8 + 15) / 16 * 16;
+  const long long strip = (long long)kStripRows * Wo * (16 * nb + 4) * 4;
+  const long long all = img + strip + kStemWaves * nb * 16;
+  if (all > (long long)kLdsBytes) return 0;
+  *strip_off = (int)img;
+  *red_off = (int)(img + strip);
+  return (int)all;
+}
+const void* stem_fn(int nb) {
+  return nb == 4 ? reinterpret_cast<const void*>(&stem_kernel<4>) : reinterpret_cast<const void*>(&stem_kernel<1>);
+}
+
+hipError_t launch_stem(const evo_encoder* e, const ConvLayer& L, const float* images, int N, float* yf, __bf16* yb,
+                       hipStream_t st) {
+  const evo_encoder_desc& d = e->desc;
+  const auto magic = [](int v) { return (uint32_t)(((uint64_t(1) << 32) + v - 1) / v); };
+  StemArgs a;
+  const int lds = stem_lds(d, e->stem_nb, &a.strip_off, &a.red_off);
+  a.x = images;
+  a.w = reinterpret_cast<const uint4*>(L.w);
+  a.gamma = L.gamma;
+  a.beta = L.beta;
+  a.yf = yf;
+  a.yb = yb;
+  a.H = d.height;
+  a.W = d.width;
+  a.Cin = d.in_ch;
+  a.Ho = out_size(d.height, 7, 2, 3);
+  a.Wo = out_size(d.width, 7, 2, 3);
+  a.Hp = out_size(a.Ho, 3, 2, 1);
+  a.Wp = out_size(a.Wo, 3, 2, 1);
+  a.C = L.cout;
+  a.PW = stem_pitch(d.width);
+  a.PR = 2 * (a.Ho - 1) + 7;
+  a.nt = L.cout / (16 * e->stem_nb);
+  a.div_pw = magic(a.PW);
+  a.div_wo = magic(a.Wo);
+  a.div_wp = magic(a.Wp);
+  a.eps = 1e-5f;
+  void* args[] = {&a};
+  return hipLaunchKernel(stem_fn(e->stem_nb), dim3((unsigned)(N * a.nt)), dim3(kStemWaves * 64), args, (size_t)lds, st);
 }
 
 // The conv result lands in `y` (one split) or as partials in the encoder's
@@ -964,13 +1676,58 @@ int evo_create_encoder(const evo_encoder_desc* desc, const float* host_weights, 
     ENC_TRY(hipMalloc(&e->d_raw, n_floats * sizeof(float)));
     ENC_TRY(hipMemcpy(e->d_raw, host_weights, n_floats * sizeof(float), hipMemcpyHostToDevice));
     e->convs = enc_layers(desc);
+    // every layer after the stem fused, or none (see conv_gn_kernel): bf16
+    // operands, groups of 16 channels, and an arrangement for every layer
+    e->fused = e->bf && desc->gn_group == 16;
+    {
+      int n_cu = 256;
+      hipDeviceProp_t prop;
+      if (hipGetDeviceProperties(&prop, e->device) == hipSuccess) n_cu = prop.multiProcessorCount;
+      int h = out_size(out_size(desc->height, 7, 2, 3), 3, 2, 1), w = out_size(out_size(desc->width, 7, 2, 3), 3, 2, 1);
+      size_t i = 1;
+      int cin = desc->stem_ch;
+      for (int s = 0; s < desc->n_stages; ++s)
+        for (int b = 0; b < desc->blocks[s]; ++b) {
+          ConvLayer& La = e->convs[i++];
+          ConvLayer& Lb = e->convs[i++];
+          const int ho = out_size(h, 3, La.stride, 1), wo = out_size(w, 3, La.stride, 1);
+          e->fused = e->fused && plan_fused(desc->max_batch, La, h, w, false, n_cu, &La.fp) &&
+                     plan_fused(desc->max_batch, Lb, ho, wo,
+                                s == desc->n_stages - 1 && b == desc->blocks[s] - 1, n_cu, &Lb.fp);
+          if (La.stride != 1 || cin != Lb.cout) {
+            ConvLayer& Ld = e->convs[i++];
+            e->fused = e->fused && plan_fused(desc->max_batch, Ld, h, w, false, n_cu, &Ld.fp);
+          }
+          h = ho;
+          w = wo;
+          cin = Lb.cout;
+        }
+    }
+    // the stem fused too where the image fits LDS: all channels a workgroup
+    // where the images alone fill the device, else one group (more
+    // workgroups, each with the whole image)
+    if (e->fused && desc->in_ch <= 4 && desc->width >= 12 && desc->stem_ch % 64 == 0) {
+      int so, ro;
+      const int nb = desc->max_batch >= 128 ? 4 : 1;
+      if (stem_lds(*desc, nb, &so, &ro)) e->stem_nb = nb;
+    }
     const int KS = e->bf ? ConvStep<__bf16>::KS : ConvStep<float>::KS;
     size_t off = 0;
     for (ConvLayer& L : e->convs) {
       L.K = L.k * L.k * L.cin;
       L.Kp = (L.K + KS - 1) / KS * KS;
-      ENC_TRY(hipMalloc(&L.w, (size_t)L.cout * L.Kp * (e->bf ? 2 : 4)));
-      hipLaunchKernelGGL(pack_conv_kernel, dim3(grid_for((long long)L.cout * L.Kp)), dim3(256), 0, 0,
+      // (the fused stem's 7 fragments of 32 a channel block exceed Kp for few image channels)
+      ENC_TRY(hipMalloc(&L.w, (size_t)L.cout * (e->stem_nb && L.k == 7 ? std::max(L.Kp, 7 * 32) : L.Kp) * (e->bf ? 2 : 4)));
+      if (e->fused && L.k != 7) {
+        hipLaunchKernelGGL(pack_fused_kernel, dim3(grid_for((long long)L.cout * L.K / 8)), dim3(256), 0, 0, e->d_raw + off,
+                           L.cout, L.cin, L.k * L.k, reinterpret_cast<uint4*>(L.w));
+        ENC_TRY(hipFuncSetAttribute(fused_kernel(L.fp.cfg, L.k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
+      } else if (e->stem_nb && L.k == 7) {
+        hipLaunchKernelGGL(pack_stem_kernel, dim3(grid_for(7ll * L.cout * 4)), dim3(256), 0, 0, e->d_raw + off, L.cout, L.cin,
+                           reinterpret_cast<uint4*>(L.w));
+        ENC_TRY(hipFuncSetAttribute(stem_fn(e->stem_nb), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
+      } else
+        hipLaunchKernelGGL(pack_conv_kernel, dim3(grid_for((long long)L.cout * L.Kp)), dim3(256), 0, 0,
                          e->d_raw + off, L.cout, L.K, L.Kp, e->bf, L.w);
       ENC_TRY(hipGetLastError());
       off += (size_t)L.cout * L.K;
@@ -1021,12 +1778,51 @@ int evo_encode(evo_encoder* e, int32_t batch, const float* images, float* featur
   // stem: conv 7x7/2, then GroupNorm + ReLU + max pool 3x3/2 in one apply pass
   {
     const ConvLayer& L = e->convs[li++];
-    ENC_HIP(launch_conv(e, L, images, batch, H, W, Y, &Ho, &Wo, &g, st));
-    ENC_HIP(launch_gn(e, L, g, batch, Ho, Wo, nullptr, 1, GN_MAXPOOL, X, 0, st));
+    if (e->stem_nb) {
+      Ho = out_size(H, 7, 2, 3);
+      Wo = out_size(W, 7, 2, 3);
+      ENC_HIP(launch_stem(e, L, images, batch, X, reinterpret_cast<__bf16*>(Z), st));
+    } else {
+      ENC_HIP(launch_conv(e, L, images, batch, H, W, Y, &Ho, &Wo, &g, st));
+      g.yb = e->fused ? reinterpret_cast<__bf16*>(Z) : nullptr;
+      ENC_HIP(launch_gn(e, L, g, batch, Ho, Wo, nullptr, 1, GN_MAXPOOL, X, 0, st));
+    }
     H = out_size(Ho, 3, 2, 1);
     W = out_size(Wo, 3, 2, 1);
   }
   int cin = d.stem_ch;
+  if (e->fused) {
+    // block input: fp32 in X (where an identity shortcut reads it) and
+    // rounded in xb; the inner activation only rounded, in yb; a projected
+    // shortcut in fp32 in Y.  A block's output may take its input's place:
+    // every element is read by the thread that writes it.
+    __bf16 *xb = reinterpret_cast<__bf16*>(Z), *yb = reinterpret_cast<__bf16*>(R);
+    for (int s = 0; s < d.n_stages; ++s)
+      for (int b = 0; b < d.blocks[s]; ++b) {
+        const int c = d.widths[s];
+        const bool last = s == d.n_stages - 1 && b == d.blocks[s] - 1;
+        const ConvLayer& La = e->convs[li++];
+        const ConvLayer& Lb = e->convs[li++];
+        const bool proj = La.stride != 1 || cin != c;
+        int H2, W2, H3, W3;
+        ENC_HIP(launch_fused(La, xb, batch, H, W, &H2, &W2, nullptr, 1, nullptr, yb, nullptr, 0, st));
+        const float* shortcut = X;
+        if (proj) {
+          int Hd, Wd;
+          ENC_HIP(launch_fused(e->convs[li++], xb, batch, H, W, &Hd, &Wd, nullptr, 0, Y, nullptr, nullptr, 0, st));
+          shortcut = Y;
+        }
+        const bool next_identity = !last && b + 1 < d.blocks[s];  // (a stage's first block projects its shortcut)
+        ENC_HIP(launch_fused(Lb, yb, batch, H2, W2, &H3, &W3, shortcut, 1, next_identity ? X : nullptr,
+                             last ? nullptr : xb, last ? features_out : nullptr, out_stride, st));
+        H = H3;
+        W = W3;
+        cin = c;
+      }
+    ENC_HIP(hipEventRecord(e->ev_done, st));
+    e->launched = true;
+    return EVO_OK;
+  }
   for (int s = 0; s < d.n_stages; ++s)
     for (int b = 0; b < d.blocks[s]; ++b) {
       const int c = d.widths[s];

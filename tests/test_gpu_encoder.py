@@ -256,3 +256,33 @@ def test_encoder_bench_batch_sampled_frames(dtype):
     else:
         print("bench batch bf16 rel", _rel(got, want))
         assert _rel(got, want) <= 3e-2
+
+
+@pytest.mark.parametrize("size,planned,batch", [((84, 84), 512, 7), ((96, 96), 512, 3), ((84, 84), 100, 9),
+                                                ((96, 96), 40, 5), ((84, 84), 1, 1), ((61, 40), 300, 6),
+                                                ((33, 97), 3, 3), ((12, 12), 64, 5)])
+def test_encoder_fused_layers(size, planned, batch):
+    """The fused stem and conv + GroupNorm layers (bf16, groups of 16, widths
+    of 64 and more) under the plans of several max_batch values: whole and
+    half-empty workgroups of several images (a batch that is no multiple of
+    the images a workgroup takes), maps from 576 pixels to 2 x 2, odd and
+    non-square sizes, 1x1 projections with and without a stride; against the
+    oracle, and bit for bit the same for an image at another place of another
+    batch.  The bound is the bf16 encoder bar above (each of the 12
+    convolutions rounds its input to 8 bits: 12^1/2 * 2^-9 = 7e-3 of
+    independent errors, normwise)."""
+    torch = _torch()
+    from paper_2607_20293_amd import evo
+    e = I.EncoderShape(*size, in_ch=3, widths=(128, 64, 128, 256) if size == (12, 12) else (64, 128, 256, 512),
+                       blocks=(1, 2, 1, 1))
+    w = I.make_encoder_weights(e, 31, "perturbed")
+    imgs = I.make_images(e, batch, 31)
+    enc = evo.Encoder(e, w, "bf16", max_batch=planned)
+    got = enc.encode(torch.from_numpy(imgs).cuda()).cpu().numpy()
+    rev = enc.encode(torch.from_numpy(imgs[::-1].copy()).cuda()).cpu().numpy()
+    one = enc.encode(torch.from_numpy(np.ascontiguousarray(imgs[-1:])).cuda()).cpu().numpy()
+    enc.close()
+    want = E.encode(e, I.split_encoder_weights(e, w), imgs, "bf16")
+    print(f"[gpu] encoder {size} planned for {planned}, batch {batch}: rel {_rel(got, want):.2e}", flush=True)
+    assert _rel(got, want) <= 3e-2
+    assert np.array_equal(got, rev[::-1]) and np.array_equal(got[-1], one[0])
