@@ -909,17 +909,23 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
     for (int m = 0; m < G; ++m)
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) acc[m][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < K1; ++k) {
-      uint4 a[RB];
+    // (the operand rows of a k-step are read one step ahead)
+    uint4 a[2][RB];
+    const auto aload = [&](int k) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
-        a[rb] = *reinterpret_cast<const uint4*>(xa + (rb * 16 + lc) * LDA + k * O::KF + lq * O::VE);
+        a[k & 1][rb] = *reinterpret_cast<const uint4*>(xa + (rb * 16 + lc) * LDA + k * O::KF + lq * O::VE);
+    };
+    aload(0);
+#pragma unroll
+    for (int k = 0; k < K1; ++k) {
+      if (k + 1 < K1) aload(k + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int m = 0; m < G; ++m) {
         const int i = (grp * K1 + k) * G + m;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) O::mma(acc[m][rb], ring[i % P], a[rb]);
+        for (int rb = 0; rb < RB; ++rb) O::mma(acc[m][rb], ring[i % P], a[k & 1][rb]);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -930,17 +936,22 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   // stage 2: acc[c] += this wave's column blocks over the group's columns
   const auto stage2 = [&](auto ty, uint4 (&ring)[P], auto& acc, const AT* z, const Seq& s, const Seq& nx, bool more) {
     constexpr int TY = decltype(ty)::value;
-#pragma unroll
-    for (int k = 0; k < C::k2(TY); ++k) {
-      uint4 a[RB];
+    uint4 a[2][RB];
+    const auto aload = [&](int k) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
-        a[rb] = *reinterpret_cast<const uint4*>(z + (rb * 16 + lc) * LDZ + k * O::KF + lq * O::VE);
+        a[k & 1][rb] = *reinterpret_cast<const uint4*>(z + (rb * 16 + lc) * LDZ + k * O::KF + lq * O::VE);
+    };
+    aload(0);
+#pragma unroll
+    for (int k = 0; k < C::k2(TY); ++k) {
+      if (k + 1 < C::k2(TY)) aload(k + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int c = 0; c < CBW; ++c) {
         const int i = C::s1(TY) + k * CBW + c;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) O::mma(acc[c][rb], ring[i % P], a[rb]);
+        for (int rb = 0; rb < RB; ++rb) O::mma(acc[c][rb], ring[i % P], a[k & 1][rb]);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
