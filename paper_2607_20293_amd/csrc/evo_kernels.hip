@@ -329,11 +329,13 @@ struct Cfg {
   static constexpr int kbt2(int ty) { return ty == 2 ? DFF / KF : K1; }  // fragments per column block, stage 2
   static constexpr int s1(int ty) { return K1 * m1(ty); }
   static constexpr int total(int ty) { return s1(ty) + k2(ty) * CBW; }
-  // ring size: 16 fragments a wave, or what divides a short sequence (8
-  // waves: 128 KiB in flight per CU; Push-T batch 1 with bf16 operands 3.54,
-  // 3.42, 3.35, 3.35 ms with 4, 8, 16, 32; width 768 at batch 128 38.8, 37.2,
-  // 37.1, 55.7 ms: more spills)
-  static constexpr int PLIM = 16;
+  // ring size: 16 fragments a wave (128 KiB in flight per CU; Push-T batch 1
+  // with bf16 operands 3.54, 3.42, 3.35, 3.35 ms with 4, 8, 16, 32), or what
+  // divides a short sequence.  Width 768: 8, which leaves registers for the
+  // running layer sums (batch 128 37.6 ms with 16 or 8 and
+  // the sums in memory, 47.4 ms with 16 and the sums in registers, 35.7 ms
+  // with 8)
+  static constexpr int PLIM = D > 256 ? 8 : 16;
   static constexpr int ring_size() {
     int p = PLIM;
     while (p > 1 && (total(0) < p || total(1) < p || total(2) < p || total(0) % p || total(2) % p)) p /= 2;
@@ -521,9 +523,6 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   constexpr bool EMB_LDS = RB == 1 && CBW <= 4 && (sizeof(AT) == 2 || TEAM > 1 || D <= 64);
   constexpr bool KEEP_EMB = RB == 1 && CBW <= 4 && !EMB_LDS;
   constexpr bool PB_LDS = EMB_LDS && (TEAM > 1 || D <= 64);  // else the row biases stay in registers
-  // layer-merged residual sum accumulated in registers, else in its cache slot
-  constexpr bool MAC_REG = CBW * RB <= 4;
-  static_assert(MAC_REG || SPT == 1 || sizeof(AT) == 4, "bf16 layer sums in memory need one sample per tile");
   constexpr float kScale = (DH == 64) ? 0.125f : (DH == 32 ? 0.17677669529663688f : 0.0f);
   static_assert(DH == 64 || DH == 32, "head dim");
 
@@ -713,8 +712,8 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   const auto cidx = [&](int unit, int c, int rb) {
     return (size_t)unit * (R * D) + ((size_t)((w * RB + rb) * CBW + c) * 64 + lane) * 4;
   };
-  // Cache-policy bits of the residual-cache accesses (and of the layer
-  // sums kept in cache slots and the memory tokens' keys and values).  At
+  // Cache-policy bits of the residual-cache accesses (and of the memory
+  // tokens' keys and values).  At
   // width 768 a unit's weights exceed an XCD's L2 and a cached residual is
   // 48 KiB, so these reads and writes are non-temporal (evicted first) and
   // leave the L2 to the weights; at width 256 the default policy measured
@@ -791,11 +790,12 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) bout[i] = 4 * lq + i < A ? raw[p.b_out + 4 * lq + i] : 0.f;
 
-  f32x4 h[CBW][RB], mac[MAC_REG ? CBW : 1][MAC_REG ? RB : 1];
+  // residual stream, and the running sum of a layer-merged cache's residuals
+  f32x4 h[CBW][RB], mac[CBW][RB];
 #pragma unroll
-  for (int c = 0; c < (MAC_REG ? CBW : 1); ++c)
+  for (int c = 0; c < CBW; ++c)
 #pragma unroll
-    for (int rb = 0; rb < (MAC_REG ? RB : 1); ++rb) mac[c][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < RB; ++rb) mac[c][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // LayerNorm gain/shift and output bias of the next unit to evaluate, for
   // this lane's columns.  Width 256: loaded one unit ahead, and every
@@ -1539,29 +1539,6 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) r[c][rb] += rbias[c];
 
-      // Layer sums kept in memory (tiles too wide for registers): the
-      // unit's partial layer sums are read in one batch through the cache's
-      // buffer resource before any is written (element by element, every
-      // load would wait for the store before it); an entry that is not
-      // needed reads past the end of the resource (zeros, no memory access)
-      const int lacc_base = CE == 4 ? (int)(cidx(3 * l + 2, 0, 0) * 4) : (int)((size_t)(3 * l) * (R * D) * 2 + cidx(0, 0, 0) * 4);
-      const auto lacc_cst = [](int c, int rb) { return (rb * CBW + c) * 1024; };
-      f32x4 lsum[MAC_REG ? 1 : CBW][MAC_REG ? 1 : RB];
-      if constexpr (!MAC_REG) {
-#pragma unroll
-        for (int c = 0; c < CBW; ++c)
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb) {
-            const int j = jrow[rb];
-            bool mg = mmg[0];
-#pragma unroll
-            for (int jj = 1; jj < SPT; ++jj)
-              if (j == jj) mg = mmg[jj];
-            const bool need = u > 0 && mg && ((pick(mev, j) >> e) & 1ull);
-            lsum[c][rb] = __builtin_bit_cast(
-                f32x4, __builtin_amdgcn_raw_buffer_load_b128(crs, need ? lacc_base : 0x7FFFFFF0, lacc_cst(c, rb), CPOL));
-          }
-      }
       // Eq. 1 per sample at unit e: evaluated residual (and cache refresh) or
       // the residual cached at the unit's most recent refresh.
 #pragma unroll
@@ -1576,28 +1553,8 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
             if (j == jj) mg = mmg[jj];
           if (pick(mev, j) & bit) {
             const f32x4 v = r[c][rb];
-            if constexpr (MAC_REG) {
-              if (mg) mac[c][rb] = (u == 0) ? v : mac[c][rb] + v;
-              if (pick(mst, j) & bit) cstore(e, c, rb, mg ? mac[c][rb] : v);
-            } else if (mg) {
-              // layer sum accumulated in memory, in fp32: in the FFN
-              // position's slot (fp32 caches) or across the SA and CA slots,
-              // which a merged layer leaves unused (fp16 caches; one sample
-              // per tile, so no other sample's rows share them); the sum of
-              // the three residuals is stored at the FFN position
-              const f32x4 sum = (u == 0) ? v : lsum[c][rb] + v;
-              if (CE == 4 || u < 2) {
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, sum), crs, lacc_base, lacc_cst(c, rb), CPOL);
-              } else if (pick(mst, j) & bit) {
-                if constexpr (CE == 2)
-                  __builtin_amdgcn_raw_buffer_store_b64(u32x2{f16x2_sat(sum[0], sum[1]), f16x2_sat(sum[2], sum[3])}, crs,
-                                                        (int)(cidx(e, 0, 0) * 2), (rb * CBW + c) * 512, CPOL);
-                else
-                  cstore(e, c, rb, sum);
-              }
-            } else if (pick(mst, j) & bit) {
-              cstore(e, c, rb, v);
-            }
+            if (mg) mac[c][rb] = (u == 0) ? v : mac[c][rb] + v;
+            if (pick(mst, j) & bit) cstore(e, c, rb, mg ? mac[c][rb] : v);
             h[c][rb] += v;
             if (p.acts != nullptr && member == 0) {
               // activation record of the uncached policy (Sec. 3.3): a[sample][unit][step][H][d]
