@@ -399,12 +399,16 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
       // team variants (one sample per tile, `team` workgroups per tile) for
       // batches that fill at most n_cu workgroups; they need cooperative
       // launch.  A team size t serves batches up to n_cu / t, the largest
-      // compiled size that fits being chosen.  With bf16 operands the
-      // automatic choice keeps only the smallest size: teams of 2 measured
-      // faster than teams of 4 at every batch (Push-T shape, 25% density:
-      // 3.57 and 3.63 ms at batch 1 and 64 against 3.65 and 4.06 ms), while
-      // with fp32 operands teams of 4 are far ahead wherever they fit
-      // (6.7-6.8 ms against 9.3-9.5 ms up to batch 64).
+      // compiled size that fits being chosen.  With bf16 operands at width
+      // 256 the automatic choice keeps only the smallest size: teams of 2
+      // measured faster than teams of 4 at every batch (Push-T shape, 25%
+      // density: 3.57 and 3.63 ms at batch 1 and 64 against 3.65 and 4.06
+      // ms), while with fp32 operands teams of 4 are far ahead wherever they
+      // fit (6.7-6.8 ms against 9.3-9.5 ms up to batch 64).  At width 768
+      // teams of 6 serve batches up to n_cu / 9: the members' exchange takes
+      // longer the more teams share the memory (10% density, 6 against 2
+      // members: batch 1 14.0 and 17.8 ms, 20 15.7 and 17.3, 26 16.5 and
+      // 17.3, 32 17.6 and 17.3, 42 19.6 and 17.4).
       // EVO_TEAM=0 switches teams off, EVO_TEAM=<size> keeps only that size.
       const char* env = std::getenv("EVO_TEAM");
       const int team_only = env ? std::atoi(env) : -1;
@@ -417,7 +421,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
         for (int i = 0; i < nsz; ++i)
           if (sizes[i] == team_only) sizes[k++] = sizes[i];
         nsz = k;
-      } else if (s.dtype == EVO_BF16 && nsz > 1) {
+      } else if (s.dtype == EVO_BF16 && s.d == 256 && nsz > 1) {
         sizes[0] = sizes[nsz - 1];  // sizes are sorted descending
         nsz = 1;
       }
@@ -430,7 +434,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
         for (int i = nsz - 1; i >= 0; --i) {  // smallest team (largest batches) last in `teams`
           const int t = sizes[i];
           if (p->n_cu < t) continue;
-          const int cap = p->n_cu / t;
+          const int cap = s.d > 256 && t > 2 ? p->n_cu / 9 : p->n_cu / t;
           evo_policy::TeamCfg tc;
           tc.team = t;
           tc.max_batch = std::min(s.max_batch, std::max(cap, 1));
@@ -438,7 +442,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
           p->teams.insert(p->teams.begin(), tc);
           rows = std::max(rows, (size_t)tc.max_batch * t * s.H);
           if (!fold) okv_floats = std::max(okv_floats, tc.okv_stride * t);  // fold records: one shared copy
-          xchg_rows = std::max(xchg_rows, (size_t)tc.max_batch * t * s.H);
+          xchg_rows = std::max(xchg_rows, (size_t)tc.max_batch * kernel_team_slots(t, s.d) * s.H);
           ctr_tiles = std::max(ctr_tiles, (size_t)tc.max_batch);
         }
       }
@@ -449,7 +453,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
       if (const size_t n = redundancy_workspace_floats(s.max_batch, U, T, (long long)s.H * d, p->n_cu))
         CREATE_TRY(hipMalloc(&p->d_rws, n * sizeof(float)));
       if (!p->teams.empty()) {
-        CREATE_TRY(hipMalloc(&p->d_xchg, xchg_rows * 3 * d * sizeof(float)));
+        CREATE_TRY(hipMalloc(&p->d_xchg, xchg_rows * d * sizeof(float)));
         CREATE_TRY(hipMalloc(&p->d_tctr, ctr_tiles * 16 * sizeof(unsigned)));
         CREATE_TRY(hipMalloc(&p->d_derr, sizeof(unsigned)));
         CREATE_TRY(hipMemset(p->d_derr, 0, sizeof(unsigned)));
@@ -613,18 +617,31 @@ static int denoise_impl(evo_policy* p, int32_t batch, const float* obs_cond, con
       if (!base) return fail(EVO_E_HIP, "the device scratch array has no address on device %d", p->device);
       const auto al = [](size_t v) { return (v + 255) / 256 * 256; };
       const size_t okv_per = (size_t)s.L * s.n_obs * (fold ? s.fold_rec() : 2 * s.d);
-      const size_t okv_copies = (fold || team == 1) ? 1 : (size_t)team;
-      size_t off = 0;
-      const size_t o_plan = off;
-      off += al(2 * al(ntile_ent * sizeof(int32_t)) + (size_t)ps.n_used * ucodes);
-      const size_t o_cache = off;
-      off += al((size_t)ps.n_tiles * team * s.U() * R * D * s.cache_elt());
-      const size_t o_okv = off;
-      off += al(okv_copies * batch * okv_per * sizeof(float));
-      const size_t o_xchg = off;
-      if (team > 1) off += al((size_t)ps.n_tiles * 3 * team * R * D * sizeof(float));
-      const size_t o_ctr = off;
-      off += al(((size_t)ps.n_tiles * 16 + 1) * sizeof(unsigned));
+      size_t off, o_plan, o_cache, o_okv, o_xchg, o_ctr;
+      const auto carve = [&]() {
+        off = 0;
+        o_plan = off;
+        off += al(2 * al(ntile_ent * sizeof(int32_t)) + (size_t)ps.n_used * ucodes);
+        o_cache = off;
+        off += al((size_t)ps.n_tiles * team * s.U() * R * D * s.cache_elt());
+        o_okv = off;
+        off += al(((fold || team == 1) ? 1 : (size_t)team) * batch * okv_per * sizeof(float));
+        o_xchg = off;
+        if (team > 1) off += al((size_t)ps.n_tiles * kernel_team_slots(team, s.d) * R * D * sizeof(float));
+        o_ctr = off;
+        off += al(((size_t)ps.n_tiles * 16 + 1) * sizeof(unsigned));
+      };
+      carve();
+      // width 768: a team whose members' copies do not fit gives way to the
+      // next smaller one (down to two, so that every batch fits that teams
+      // of two would)
+      while (off > kScratchBytes && s.d > 256 && tc && tc + 1 < p->teams.data() + p->teams.size() && batch <= tc[1].max_batch) {
+        ++tc;
+        team = tc->team;
+        int th;
+        if (kernel_available(KernelKey{s.d, s.dh(), s.H, s.dff, s.dtype, 1, team}, &th)) threads = th;
+        carve();
+      }
       if (off > kScratchBytes)
         return fail(EVO_E_UNSUPPORTED,
                     "evo_denoise_noalloc: batch %d needs %zu bytes of device scratch, the array holds %zu "

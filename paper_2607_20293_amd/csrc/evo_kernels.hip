@@ -665,31 +665,53 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   // the partials of the n-th evaluated unit.  A slot word that still holds
   // the sentinel has not been written yet; every member resets its own slot
   // of unit n-1 once it holds all partials of unit n (then every member has
-  // finished reading unit n-1), which is the slot's next use at unit n+2.
+  // finished reading unit n-1), before its next use at unit n+2.
   // SC1 cache-policy bit: device-coherent access; at width 768 also the
   // non-temporal bit, so that the exchange traffic (three 96 KiB slots per
   // member and unit) does not displace the weights from the L2
   constexpr int kCoherent = D > 256 ? (16 | 2) : 16;
   constexpr unsigned kEmpty = 0xFFFFFFFFu;  // never produced by arithmetic (canonical NaN differs)
   int nbar = 0;                             // evaluated units exchanged so far
-  float* const xb = TEAM > 1 ? p.xchg + (size_t)tile * (3 * TEAM) * (R * D) : nullptr;
-  const auto xr = __builtin_amdgcn_make_buffer_rsrc(xb, (short)0, TEAM > 1 ? 3 * TEAM * R * D * 4 : 0, 0x00020000);
+  // Teams of more than two on a tile too wide to read every member's whole
+  // partial (SCATTER): each member sums its share of the column blocks and
+  // publishes the sums in a result slot beside the members' slots, so it
+  // reads about two partials' worth a unit instead of TEAM - 1 (width 768,
+  // teams of 6: 176 KiB instead of 480).
+  constexpr bool SCATTER = TEAM > 2 && CBW * RB > 4;
+  static_assert(!SCATTER || CBW % TEAM == 0, "column blocks per member");
+  // SCATTER has a fourth slot, so that a slot is emptied two units after its
+  // use, together with the stores of that unit's partials (the stores that
+  // empty a slot of the unit just summed would be waited for by the next
+  // unit's first loads)
+  constexpr int XM = SCATTER ? TEAM + 1 : TEAM, OWN = SCATTER ? CBW / TEAM : 1, XS = SCATTER ? 4 : 3;
+  float* const xb = TEAM > 1 ? p.xchg + (size_t)tile * (XS * XM) * (R * D) : nullptr;
+  const auto xr = __builtin_amdgcn_make_buffer_rsrc(xb, (short)0, TEAM > 1 ? XS * XM * R * D * 4 : 0, 0x00020000);
   // byte offset of this lane's fragment (c, rb) in a member's slot, split
   // into a per-lane part (VGPR) and a constant part (SGPR), so that a wide
   // tile does not hold one offset register per fragment
-  const auto xoff = [&](int slot, int m) { return ((slot * TEAM + m) * (R * D) + (w * RB * CBW * 64 + lane) * 4) * 4; };
+  const auto xoff = [&](int slot, int m) { return ((slot * XM + m) * (R * D) + (w * RB * CBW * 64 + lane) * 4) * 4; };
   const auto xcst = [](int c, int rb) { return (rb * CBW + c) * 1024; };
+  // Stores take the whole offset in the VGPR: with an SGPR offset the compiler
+  // leaves out the wait states between a 16-byte store and the next write of
+  // its data registers, and the last four lanes of each sixteen then stored
+  // the new contents (seen when that write was the very next instruction)
+  const auto xstore = [&](u32x4 v, int slot, int m, int c, int rb) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, xr, xoff(slot, m) + xcst(c, rb), 0, kCoherent);
+  };
   if constexpr (TEAM > 1) {
     // all three slots of this member start empty; one counter barrier makes
     // sure no member reads a slot before its owner has emptied it
     const u32x4 empty = {kEmpty, kEmpty, kEmpty, kEmpty};
 #pragma unroll
-    for (int sl = 0; sl < 3; ++sl)
+    for (int sl = 0; sl < XS; ++sl)
 #pragma unroll
       for (int c = 0; c < CBW; ++c)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-          __builtin_amdgcn_raw_buffer_store_b128(empty, xr, xoff(sl, member), xcst(c, rb), kCoherent);
+        for (int rb = 0; rb < RB; ++rb) {
+          xstore(empty, sl, member, c, rb);
+          if (SCATTER && c / OWN == member)
+            xstore(empty, sl, TEAM, c, rb);
+        }
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
     if (tid == 0) {
@@ -1423,26 +1445,47 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
         // ready once it no longer holds the sentinel.  Waits are bounded;
         // on a timeout the device error flag is set and every later wait
         // ends at once, so the kernel always finishes.
-        const int cur = nbar % 3, prev = (nbar + 2) % 3;
+        const int cur = nbar % XS, prev = (nbar + 2) % XS;  // prev: the last unit's slot, or with four the one before
+        const u32x4 empty = {kEmpty, kEmpty, kEmpty, kEmpty};
+        const auto empty_prev = [&]() {
+#pragma unroll
+          for (int c = 0; c < CBW; ++c)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+              xstore(empty, prev, SCATTER && c / OWN == member ? TEAM : member, c, rb);
+        };
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the reset of this slot (one unit ago) has landed
+        // (a word equal to the sentinel becomes the canonical NaN)
+        const auto canonical = [&](f32x4 x) {
+          u32x4 v = __builtin_bit_cast(u32x4, x);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = v[q] == kEmpty ? 0x7FC00000u : v[q];
+          return v;
+        };
 #pragma unroll
         for (int c = 0; c < CBW; ++c)
 #pragma unroll
           for (int rb = 0; rb < RB; ++rb) {
-            u32x4 v = __builtin_bit_cast(u32x4, r[c][rb]);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = v[q] == kEmpty ? 0x7FC00000u : v[q];
-            if (!(p.withhold && member == 0))
-              __builtin_amdgcn_raw_buffer_store_b128(v, xr, xoff(cur, member), xcst(c, rb), kCoherent);
+            const u32x4 v = canonical(r[c][rb]);
+            if (!(p.withhold && member == 0) && !(SCATTER && c / OWN == member))
+              xstore(v, cur, member, c, rb);
           }
+        // (this unit was reached, so every member has read everything of the
+        // unit before the last)
+        if constexpr (SCATTER) empty_prev();
         // bounded wait for every word of `v` (loaded by `load`) to be written;
         // polls back to back (each is a memory round trip), the error flag
-        // and the limit are checked every 32 polls
+        // and the limit are checked every 32 polls.  Width 256: the wave polls
+        // until every lane's words are there (one scalar branch; Push-T batch
+        // 1 and 64 with bf16 operands 3.37 and 3.39 ms, with lanes leaving one
+        // by one 3.40 and 3.42); width 768 the reverse (batch 1 and 128 24.6
+        // and 36.6 ms, against 24.1 and 36.1).
+        const auto arrived = [](bool ok) { return D > 256 ? ok : __builtin_amdgcn_ballot_w64(!ok) == 0; };
         const auto poll = [&](auto& v, auto load, auto ready) {
           unsigned spins = 0;
           while (true) {
             load(v);
-            if (ready(v)) break;
+            if (arrived(ready(v))) break;
             if ((++spins & 31u) == 0u &&
                 (__hip_atomic_load(p.derr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u || spins > p.spin_limit)) {
               __hip_atomic_store(p.derr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1484,6 +1527,75 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
 #pragma unroll
               for (int rb = 0; rb < RB; ++rb) r[c0 + c][rb] += __builtin_bit_cast(f32x4, part[c][rb]);
           }
+        } else if constexpr (SCATTER) {
+          // this member's column blocks: its own partial from registers, the
+          // others' from their slots, summed in member order
+          f32x4 own[OWN][RB];
+#pragma unroll
+          for (int c = 0; c < CBW; ++c)
+            if (c / OWN == member) {
+#pragma unroll
+              for (int rb = 0; rb < RB; ++rb) own[c % OWN][rb] = r[c][rb];
+            }
+          u32x4 part[TEAM][OWN][RB];
+          unsigned pending = ((1u << TEAM) - 1u) & ~(1u << member);
+          poll(part,
+               [&](u32x4 (&v)[TEAM][OWN][RB]) {
+#pragma unroll
+                 for (int m = 0; m < TEAM; ++m)
+                   if (pending >> m & 1u) {
+#pragma unroll
+                     for (int c = 0; c < OWN; ++c)
+#pragma unroll
+                       for (int rb = 0; rb < RB; ++rb)
+                         v[m][c][rb] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff(cur, m), xcst(member * OWN + c, rb), kCoherent);
+                   }
+               },
+               [&](const u32x4 (&v)[TEAM][OWN][RB]) {
+#pragma unroll
+                 for (int m = 0; m < TEAM; ++m)
+                   if (pending >> m & 1u) {
+                     bool ok = true;
+#pragma unroll
+                     for (int c = 0; c < OWN; ++c)
+#pragma unroll
+                       for (int rb = 0; rb < RB; ++rb) ok = ok && full(v[m][c][rb]);
+                     if (arrived(ok)) pending &= ~(1u << m);
+                   }
+                 return pending == 0u;
+               });
+#pragma unroll
+          for (int c = 0; c < OWN; ++c)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+              f32x4 acc = member == 0 ? own[c][rb] : __builtin_bit_cast(f32x4, part[0][c][rb]);
+#pragma unroll
+              for (int m = 1; m < TEAM; ++m)
+                acc += member == m ? own[c][rb] : __builtin_bit_cast(f32x4, part[m][c][rb]);
+              xstore(canonical(acc), cur, TEAM, member * OWN + c, rb);
+            }
+          // every member's sums (its own too)
+          u32x4 sum[CBW][RB];
+          poll(sum,
+               [&](u32x4 (&v)[CBW][RB]) {
+#pragma unroll
+                 for (int c = 0; c < CBW; ++c)
+#pragma unroll
+                   for (int rb = 0; rb < RB; ++rb)
+                     v[c][rb] = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff(cur, TEAM), xcst(c, rb), kCoherent);
+               },
+               [&](const u32x4 (&v)[CBW][RB]) {
+                 bool ok = true;
+#pragma unroll
+                 for (int c = 0; c < CBW; ++c)
+#pragma unroll
+                   for (int rb = 0; rb < RB; ++rb) ok = ok && full(v[c][rb]);
+                 return ok;
+               });
+#pragma unroll
+          for (int c = 0; c < CBW; ++c)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) r[c][rb] = __builtin_bit_cast(f32x4, sum[c][rb]);
         } else {
           // more operands: every member sums the partials in member order
           u32x4 part[TEAM][CBW][RB];
@@ -1509,7 +1621,7 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
                      for (int c = 0; c < CBW; ++c)
 #pragma unroll
                        for (int rb = 0; rb < RB; ++rb) ok = ok && full(v[m][c][rb]);
-                     if (ok) pending &= ~(1u << m);
+                     if (arrived(ok)) pending &= ~(1u << m);
                    }
                  return pending == 0u;
                });
@@ -1524,14 +1636,9 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
               r[c][rb] = acc;
             }
         }
-        // every member has read the partials of the previous unit: empty
-        // this member's slot of it for its next use
-        const u32x4 empty = {kEmpty, kEmpty, kEmpty, kEmpty};
-#pragma unroll
-        for (int c = 0; c < CBW; ++c)
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb)
-            __builtin_amdgcn_raw_buffer_store_b128(empty, xr, xoff(prev, member), xcst(c, rb), kCoherent);
+        // every member has read the partials of the previous unit: empty this
+        // member's slot of it for its next use
+        if constexpr (!SCATTER) empty_prev();
         ++nbar;
       }
 #pragma unroll
@@ -1869,7 +1976,8 @@ hipError_t launch_ddpm_table(int T, float* table, hipStream_t stream) {
   X(__bf16, 256, 64, 16, 1, 1024, 4, 1, 256, 8, 4)        \
   X(float, 256, 64, 16, 1, 1024, 8, 2, 256, 8, 2)         \
   X(__bf16, 256, 64, 16, 1, 1024, 8, 2, 512, 8, 2)        \
-  X(__bf16, 768, 64, 32, 1, 3072, 8, 2, 256, 5, 2)
+  X(__bf16, 768, 64, 32, 1, 3072, 8, 2, 256, 5, 2)        \
+  X(__bf16, 768, 64, 32, 1, 3072, 8, 2, 512, 5, 6)
 
 template <class AT> constexpr int dtype_of() { return std::is_same<AT, float>::value ? 0 : 1; }
 

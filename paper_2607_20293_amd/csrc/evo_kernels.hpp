@@ -105,9 +105,11 @@ hipError_t launch_time_fold(const float* raw, const LayerOff* loff, const float*
 // not a memset node, so that the call may be captured into a graph)
 hipError_t launch_zero_u32(unsigned* dst, int n, hipStream_t stream);
 
-// team size of the small-batch variant for a shape (1: none compiled)
 // team sizes (> 1) compiled for a shape, largest first; returns their number
 int kernel_team_sizes(const KernelKey& key, int out[4]);
+// exchange slots of a tile: three of every member's partials; at width 768 with
+// more than two members four, each with the sums too
+inline int kernel_team_slots(int team, int d) { return d > 256 && team > 2 ? 4 * (team + 1) : 3 * team; }
 
 // Eq. 6 dissimilarity scores from recorded activations acts [R][U][T][V]:
 // part [R][U][T] receives each query's term, d [U][T] their mean over R

@@ -145,6 +145,63 @@ def test_team_variant_matches_single_workgroup(dtype, size):
     pol_1.close()
 
 
+@pytest.mark.parametrize("size", [6, 2])
+@pytest.mark.parametrize("gran", [O.GRAN_UNIT, O.GRAN_LAYER])
+def test_wide_team_variants(size, gran):
+    """Width 768: teams of 6 (every member sums its sixth of the columns and
+    the sums are exchanged in a second round) and of 2, on a ragged batch with
+    mixed schedules, unit caches and layer-merged ones, against the oracle,
+    one workgroup per tile (both within the bf16 bar of the oracle, so within
+    twice the bar of each other) and themselves."""
+    from dataclasses import replace
+    s = replace(I.BIMANUAL, n_layers=2)
+    wts = I.make_weights(s, 16, "perturbed")
+    B = 5
+    obs, noise = I.make_obs(s, B, 16), I.make_noise(s, B, 16)
+    rng = np.random.default_rng([16, gran])
+    rows = s.n_layers if gran == O.GRAN_LAYER else 3 * s.n_layers
+    lats = [I.lattice_bernoulli(rows, s.n_steps, q, rng) for q in (0.2, 0.5, 1.0)]
+    ids = np.array([0, 1, 2, 1, 0], np.int32)
+    pol, got, st, _ = _case(f"wide_team{size}_gran{gran}", s, wts, obs, noise, lats, ids, "bf16", gran=gran,
+                            env={"EVO_TEAM": str(size)})
+    pol_1, got_1, st_1, _ = _case(f"wide_noteam_gran{gran}", s, wts, obs, noise, lats, ids, "bf16", gran=gran, team=False)
+    assert st_1["n_workgroups"] == B and st["n_workgroups"] in (B, size * B)
+    assert float(np.max(np.abs(got - got_1))) <= 2 * 3e-2 * max(1.0, float(np.max(np.abs(got_1))))
+    again, _ = run_gpu(pol, obs, noise, ids)
+    assert np.array_equal(again, got)
+    pol.close()
+    pol_1.close()
+
+
+def test_wide_noalloc_takes_smaller_teams():
+    """evo_denoise_noalloc at width 768: a batch whose teams of 6 exceed the
+    scratch array runs teams of 2 (as it did before teams of 6), smaller ones
+    run the same kernels as evo_denoise."""
+    import torch
+    from dataclasses import replace
+    s = I.BIMANUAL
+    wts = I.make_weights(s, 17, "perturbed")
+    dev = device()
+    pol = _policy(s, wts, "bf16", 13, 1)
+    pol.set_schedule(0, I.lattice_all(3 * s.n_layers, s.n_steps), O.GRAN_UNIT)
+    if pol.denoise(*(torch.from_numpy(f(s, 1, 17)).to(dev) for f in (I.make_obs, I.make_noise))) is None or \
+            pol.stats()["n_workgroups"] != 6:
+        pol.close()
+        pytest.skip("the team variant is not used on this device")
+    for B, wgs in ((1, 6), (3, 18), (13, 26)):
+        obs, noise = (torch.from_numpy(f(s, B, 17)).to(dev) for f in (I.make_obs, I.make_noise))
+        want = pol.denoise(obs, noise).clone()
+        out = torch.empty_like(want)
+        pol.denoise_noalloc(obs, noise, None, out)
+        pol.synchronize()
+        assert pol.stats()["n_workgroups"] == wgs
+        if wgs == 6 * B:
+            assert torch.equal(out, want)
+        else:  # both within the bf16 bar of the exact chunk
+            assert float((out - want).abs().max()) <= 2 * 3e-2 * max(1.0, float(want.abs().max()))
+    pol.close()
+
+
 @pytest.mark.parametrize("size", [4, 2])
 def test_team_wait_timeout_is_reported(size):
     """Error path of the team variant, forced from the host: team member 0
