@@ -2,7 +2,14 @@
 // GroupNorm and global average pooling (the pretrained policy's encoder,
 // which the method leaves unchanged, Sec. 3.1 and Sec. 3.4).
 //
-// Activations are NHWC fp32 in HBM.  Convolutions are implicit GEMMs on
+// Activations are NHWC fp32 in HBM.  With bf16 operands, GroupNorm groups of
+// 16 channels and widths that are multiples of 64, every layer is one kernel
+// that keeps whole images on a workgroup (conv_gn_kernel, and stem_kernel for
+// the first layer and its pooling; see there).  512 frames of 84x84: 20
+// kernels, 755 us; the general path 41 kernels, 1490 us.
+//
+// The general path (fp32, other groups or widths, maps too large for LDS) is
+// the rest of this comment.  Convolutions are implicit GEMMs on
 // MFMA: M = output pixels, N = output channels, K = kh * kw * Cin in
 // (kh, kw, Cin) order, which is the packed weight layout [Cout][Kp] (K
 // padded to the K step).  The A tile is gathered from the input with the
@@ -1085,7 +1092,7 @@ constexpr size_t kLdsBytes = 160 * 1024;
 // zero border, so a kernel row of 7 pixels plus one of weight zero is one
 // K step of 32, and an operand fragment is an aligned 16-byte read at pixel
 // 2 ow + 2 (lane / 16) of the row.  The 7 x NB weight fragments stay in
-// registers.  512 frames of 84x84: three kernels 282 us, this one STEM_NOW.
+// registers.  512 frames of 84x84: three kernels 282 us, this one 115 us.
 constexpr int kStemWaves = 8, kStripRows = 5;
 
 struct StemArgs {
@@ -1678,6 +1685,8 @@ int evo_create_encoder(const evo_encoder_desc* desc, const float* host_weights, 
     e->convs = enc_layers(desc);
     // every layer after the stem fused, or none (see conv_gn_kernel): bf16
     // operands, groups of 16 channels, and an arrangement for every layer
+    // (84x84 frames, fused and general path: 2 frames 171 and 259 us, 100
+    // frames 397 and 519 us, 512 frames 755 and 1490 us)
     e->fused = e->bf && desc->gn_group == 16;
     {
       int n_cu = 256;

@@ -523,6 +523,11 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   constexpr bool EMB_LDS = RB == 1 && CBW <= 4 && (sizeof(AT) == 2 || TEAM > 1 || D <= 64);
   constexpr bool KEEP_EMB = RB == 1 && CBW <= 4 && !EMB_LDS;
   constexpr bool PB_LDS = EMB_LDS && (TEAM > 1 || D <= 64);  // else the row biases stay in registers
+  // Operand rows read from LDS one k-step ahead: with fp32 operands (batch 37
+  // 2.99 -> 2.92 ms) and tiles of two row blocks (population of 512 9.83 ->
+  // 9.61 ms); a bf16 k-step of one row block is too short to gain by it (Push-T
+  // batch 1 3.36 ms without, 3.40 with)
+  constexpr bool KAHEAD = RB == 2 || sizeof(AT) == 4;
   constexpr float kScale = (DH == 64) ? 0.125f : (DH == 32 ? 0.17677669529663688f : 0.0f);
   static_assert(DH == 64 || DH == 32, "head dim");
 
@@ -931,18 +936,21 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
     for (int m = 0; m < G; ++m)
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) acc[m][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // (the operand rows of a k-step are read one step ahead)
     uint4 a[2][RB];
     const auto aload = [&](int k) {
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
         a[k & 1][rb] = *reinterpret_cast<const uint4*>(xa + (rb * 16 + lc) * LDA + k * O::KF + lq * O::VE);
     };
-    aload(0);
+    if constexpr (KAHEAD) aload(0);
 #pragma unroll
     for (int k = 0; k < K1; ++k) {
-      if (k + 1 < K1) aload(k + 1);
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (KAHEAD) {
+        if (k + 1 < K1) aload(k + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        aload(k);
+      }
 #pragma unroll
       for (int m = 0; m < G; ++m) {
         const int i = (grp * K1 + k) * G + m;
@@ -964,11 +972,15 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
       for (int rb = 0; rb < RB; ++rb)
         a[k & 1][rb] = *reinterpret_cast<const uint4*>(z + (rb * 16 + lc) * LDZ + k * O::KF + lq * O::VE);
     };
-    aload(0);
+    if constexpr (KAHEAD) aload(0);
 #pragma unroll
     for (int k = 0; k < C::k2(TY); ++k) {
-      if (k + 1 < C::k2(TY)) aload(k + 1);
-      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (KAHEAD) {
+        if (k + 1 < C::k2(TY)) aload(k + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        aload(k);
+      }
 #pragma unroll
       for (int c = 0; c < CBW; ++c) {
         const int i = C::s1(TY) + k * CBW + c;
