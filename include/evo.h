@@ -185,9 +185,10 @@ int evo_denoise(evo_policy* p, int32_t batch, const float* obs_cond, const float
  * data does not fit the array is refused with EVO_E_UNSUPPORTED before
  * anything is enqueued (Push-T-shaped policies: about 200 samples with bf16
  * operands, about 120 with fp32).  Policies of width 768 run small batches
- * on teams of 6 workgroups a sample; where those do not fit the array but
- * teams of 2 do (batches of about 4 to 13), this call runs teams of 2, whose
- * partial residuals are summed in another order.  Every
+ * on teams of 6 workgroups a sample; the batches (about 5 to 14) whose teams
+ * of 6 exceed the array, but would not with teams of 2, keep their data in a
+ * buffer of the policy instead, allocated at creation, with the same kernels
+ * and results.  Every
  * call on a device shares that device's array, which keeps the last call's
  * contents (each call clears what must start at zero): calls that overlap
  * on one device race (different policies, or different threads); calls of

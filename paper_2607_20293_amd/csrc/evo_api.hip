@@ -158,6 +158,10 @@ struct evo_policy {
   bool last_noalloc = false;      // the last call ran in the device scratch array
   PlanSpace plan_ws;              // plan arrays, sized at creation
   void* scratch = nullptr;        // this device's scratch array (evo_denoise_noalloc)
+  // width 768: the working data of evo_denoise_noalloc for the batches whose
+  // teams exceed the scratch array although teams of two would fit it
+  uint8_t* d_wide = nullptr;
+  size_t wide_bytes = 0;
   // optional timing of the denoising kernel alone: a ring of event pairs
   // recorded around its launch, harvested into t_ms / t_n
   static constexpr int kTimingPairs = 64;
@@ -167,6 +171,30 @@ struct evo_policy {
   double t_ms = 0.0;
   int64_t t_n = 0;
 };
+
+// Where evo_denoise_noalloc's working data lie in its array, and their size.
+struct ScratchLayout {
+  size_t plan, cache, okv, xchg, ctr, total;
+};
+static size_t align256(size_t v) { return (v + 255) / 256 * 256; }
+static ScratchLayout scratch_layout(const Shape& s, int batch, int n_tiles, int spt, int team, int n_used) {
+  const size_t R = (size_t)spt * s.H, D = s.d, tiles = n_tiles;
+  const size_t okv_per = (size_t)s.L * s.n_obs * (s.folds_ca() ? s.fold_rec() : 2 * s.d);
+  const size_t okv_copies = (s.folds_ca() || team == 1) ? 1 : (size_t)team;
+  ScratchLayout y;
+  y.plan = 0;
+  y.cache = align256(2 * align256(tiles * spt * sizeof(int32_t)) + (size_t)n_used * s.T * 3 * sizeof(uint64_t));
+  y.okv = y.cache + align256(tiles * team * s.U() * R * D * s.cache_elt());
+  y.xchg = y.okv + align256(okv_copies * batch * okv_per * sizeof(float));
+  y.ctr = y.xchg + (team > 1 ? align256(tiles * kernel_team_slots(team, s.d) * R * D * sizeof(float)) : 0);
+  y.total = y.ctr + align256((tiles * 16 + 1) * sizeof(unsigned));
+  return y;
+}
+// Width 768, teams of more than two: the scratch array takes the batches it
+// would take with teams of two (a larger team's copies may lie in d_wide).
+static bool wide_fits(const Shape& s, int batch, int n_used) {
+  return scratch_layout(s, batch, batch, 1, 2, n_used).total <= kScratchBytes;
+}
 
 namespace evo {
 const Shape& policy_shape(const evo_policy* p) { return p->s; }
@@ -193,6 +221,7 @@ static void release(evo_policy* p) {
   (void)hipFree(p->d_tctr);
   (void)hipFree(p->d_derr);
   (void)hipFree(p->d_plan);
+  (void)hipFree(p->d_wide);
   for (int i = 0; i < 2; ++i) {
     if (p->h_stage[i]) (void)hipHostFree(p->h_stage[i]);
     if (p->ev[i]) (void)hipEventDestroy(p->ev[i]);
@@ -457,6 +486,14 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
         CREATE_TRY(hipMalloc(&p->d_tctr, ctr_tiles * 16 * sizeof(unsigned)));
         CREATE_TRY(hipMalloc(&p->d_derr, sizeof(unsigned)));
         CREATE_TRY(hipMemset(p->d_derr, 0, sizeof(unsigned)));
+        const evo_policy::TeamCfg& tc = p->teams.front();
+        if (s.d > 256 && tc.team > 2) {
+          for (int b = 1; b <= tc.max_batch && wide_fits(s, b, 1); ++b) {
+            const size_t need = scratch_layout(s, b, b, 1, tc.team, std::min(s.max_sched, b)).total;
+            if (need > kScratchBytes) p->wide_bytes = need;
+          }
+          if (p->wide_bytes) CREATE_TRY(hipMalloc(&p->d_wide, p->wide_bytes));
+        }
       }
       p->tiles_cap = tiles * spt_max;
       p->codes_cap = (size_t)std::min(s.max_sched, s.max_batch) * T * 3 * sizeof(uint64_t);
@@ -599,7 +636,6 @@ static int denoise_impl(evo_policy* p, int32_t batch, const float* obs_cond, con
       return fail(EVO_E_STATE, "plan exceeds the policy's buffers");
     if (team > 1 && ps.n_tiles > tc->max_batch) return fail(EVO_E_STATE, "team plan exceeds the buffers");
     const bool fold = s.folds_ca();
-    const size_t R = (size_t)spt * s.H, D = s.d;
     CallBuffers cb;
     if (!noalloc) {
       cb.cache = p->d_cache;
@@ -615,46 +651,28 @@ static int denoise_impl(evo_policy* p, int32_t batch, const float* obs_cond, con
       // fold records), team exchange slots, team counters and error flag
       uint8_t* base = static_cast<uint8_t*>(p->scratch);
       if (!base) return fail(EVO_E_HIP, "the device scratch array has no address on device %d", p->device);
-      const auto al = [](size_t v) { return (v + 255) / 256 * 256; };
-      const size_t okv_per = (size_t)s.L * s.n_obs * (fold ? s.fold_rec() : 2 * s.d);
-      size_t off, o_plan, o_cache, o_okv, o_xchg, o_ctr;
-      const auto carve = [&]() {
-        off = 0;
-        o_plan = off;
-        off += al(2 * al(ntile_ent * sizeof(int32_t)) + (size_t)ps.n_used * ucodes);
-        o_cache = off;
-        off += al((size_t)ps.n_tiles * team * s.U() * R * D * s.cache_elt());
-        o_okv = off;
-        off += al(((fold || team == 1) ? 1 : (size_t)team) * batch * okv_per * sizeof(float));
-        o_xchg = off;
-        if (team > 1) off += al((size_t)ps.n_tiles * kernel_team_slots(team, s.d) * R * D * sizeof(float));
-        o_ctr = off;
-        off += al(((size_t)ps.n_tiles * 16 + 1) * sizeof(unsigned));
-      };
-      carve();
-      // width 768: a team whose members' copies do not fit gives way to the
-      // next smaller one (down to two, so that every batch fits that teams
-      // of two would)
-      while (off > kScratchBytes && s.d > 256 && tc && tc + 1 < p->teams.data() + p->teams.size() && batch <= tc[1].max_batch) {
-        ++tc;
-        team = tc->team;
-        int th;
-        if (kernel_available(KernelKey{s.d, s.dh(), s.H, s.dff, s.dtype, 1, team}, &th)) threads = th;
-        carve();
+      const ScratchLayout y = scratch_layout(s, batch, ps.n_tiles, spt, team, ps.n_used);
+      size_t need = y.total;
+      if (need > kScratchBytes && s.d > 256 && team > 2) {
+        need = scratch_layout(s, batch, batch, 1, 2, ps.n_used).total;
+        if (need <= kScratchBytes) {
+          if (y.total > p->wide_bytes) return fail(EVO_E_STATE, "team data exceed the policy's buffer");
+          base = p->d_wide;
+        }
       }
-      if (off > kScratchBytes)
+      if (need > kScratchBytes)
         return fail(EVO_E_UNSUPPORTED,
                     "evo_denoise_noalloc: batch %d needs %zu bytes of device scratch, the array holds %zu "
                     "(use evo_denoise, or a smaller batch)",
-                    batch, off, kScratchBytes);
-      cb.plan = base + o_plan;
-      cb.plan_tiles = al(ntile_ent * sizeof(int32_t)) / sizeof(int32_t);
-      cb.cache = reinterpret_cast<float*>(base + o_cache);
-      cb.okv = reinterpret_cast<float*>(base + o_okv);
-      cb.xchg = team > 1 ? reinterpret_cast<float*>(base + o_xchg) : nullptr;
-      cb.tctr = reinterpret_cast<unsigned*>(base + o_ctr);
+                    batch, need, kScratchBytes);
+      cb.plan = base + y.plan;
+      cb.plan_tiles = align256(ntile_ent * sizeof(int32_t)) / sizeof(int32_t);
+      cb.cache = reinterpret_cast<float*>(base + y.cache);
+      cb.okv = reinterpret_cast<float*>(base + y.okv);
+      cb.xchg = team > 1 ? reinterpret_cast<float*>(base + y.xchg) : nullptr;
+      cb.tctr = reinterpret_cast<unsigned*>(base + y.ctr);
       cb.derr = cb.tctr + (size_t)ps.n_tiles * 16;
-      cb.okv_stride = (fold || team == 1) ? 0 : batch * okv_per;
+      cb.okv_stride = (fold || team == 1) ? 0 : (size_t)batch * s.L * s.n_obs * 2 * s.d;
     }
     // Calls on a different stream than the previous one wait for it: the
     // plan, caches and observation keys/values are per-policy buffers (or

@@ -173,32 +173,36 @@ def test_wide_team_variants(size, gran):
     pol_1.close()
 
 
-def test_wide_noalloc_takes_smaller_teams():
-    """evo_denoise_noalloc at width 768: a batch whose teams of 6 exceed the
-    scratch array runs teams of 2 (as it did before teams of 6), smaller ones
-    run the same kernels as evo_denoise."""
+def test_wide_noalloc_matches_denoise():
+    """evo_denoise_noalloc at width 768: every batch it accepts runs the teams
+    that evo_denoise runs and gives the same bits, also where a team's copies
+    exceed the scratch array (they then lie in a buffer of the policy).  It
+    accepts the batches whose working data fit the array with teams of two,
+    4.72 MB a sample of this policy (14 samples), and refuses larger ones."""
     import torch
-    from dataclasses import replace
+    from paper_2607_20293_amd import evo
     s = I.BIMANUAL
     wts = I.make_weights(s, 17, "perturbed")
     dev = device()
-    pol = _policy(s, wts, "bf16", 13, 1)
-    pol.set_schedule(0, I.lattice_all(3 * s.n_layers, s.n_steps), O.GRAN_UNIT)
-    if pol.denoise(*(torch.from_numpy(f(s, 1, 17)).to(dev) for f in (I.make_obs, I.make_noise))) is None or \
-            pol.stats()["n_workgroups"] != 6:
+    pol = _policy(s, wts, "bf16", 16, 1)
+    pol.set_schedule(0, I.make_lattice("uniform", 3 * s.n_layers, s.n_steps, 0.1, 17), O.GRAN_UNIT)
+    pol.denoise(*(torch.from_numpy(f(s, 1, 17)).to(dev) for f in (I.make_obs, I.make_noise)))
+    if pol.stats()["n_workgroups"] != 6:
         pol.close()
         pytest.skip("the team variant is not used on this device")
-    for B, wgs in ((1, 6), (3, 18), (13, 26)):
+    for B in (1, 4, 5, 14, 3):
         obs, noise = (torch.from_numpy(f(s, B, 17)).to(dev) for f in (I.make_obs, I.make_noise))
         want = pol.denoise(obs, noise).clone()
+        st = pol.stats()
         out = torch.empty_like(want)
         pol.denoise_noalloc(obs, noise, None, out)
         pol.synchronize()
-        assert pol.stats()["n_workgroups"] == wgs
-        if wgs == 6 * B:
-            assert torch.equal(out, want)
-        else:  # both within the bf16 bar of the exact chunk
-            assert float((out - want).abs().max()) <= 2 * 3e-2 * max(1.0, float(want.abs().max()))
+        assert pol.stats()["n_workgroups"] == st["n_workgroups"] == 6 * B
+        assert torch.equal(out, want), B
+    obs, noise = (torch.from_numpy(f(s, 15, 17)).to(dev) for f in (I.make_obs, I.make_noise))
+    with pytest.raises(evo.EvoError) as e:
+        pol.denoise_noalloc(obs, noise, None, torch.empty((15, s.horizon, s.action_dim), device=dev))
+    assert e.value.code == -5 and "scratch" in str(e.value)
     pol.close()
 
 
