@@ -502,18 +502,28 @@ int evo_create_encoder(const evo_encoder_desc* desc, const float* host_weights, 
  * features can be written straight into a policy's observation rows);
  * other elements are not touched.  Asynchronous on hip_stream (NULL = the
  * null stream); uses the encoder's activation buffers, so calls on one
- * encoder must not overlap.  The work split (convolution K splits,
- * GroupNorm statistics chunks) is planned for max_batch, so an image's
- * features are bitwise the same at every batch size of one encoder and do
- * not depend on the other images; encoders created with different
- * max_batch may differ in the last bits.  A batch well below max_batch runs
- * that plan on fewer workgroups. */
+ * encoder must not overlap.  What decides the order of a sum (convolution K
+ * splits, GroupNorm statistics chunks) is planned for max_batch, so an
+ * image's features are bitwise the same at every batch size of one encoder
+ * and do not depend on the other images; encoders created with different
+ * max_batch may differ in the last bits.  Within that, layers that run fused
+ * split the work over workgroups for the call's batch; the others run the
+ * max_batch plan on fewer workgroups. */
 int evo_encode(evo_encoder* e, int32_t batch, const float* images, float* features_out, int32_t out_stride,
                void* hip_stream);
 
 /* Convolution FLOPs of one evo_encode of `batch` images (2 per
  * multiply-add; normalisation and pooling not counted).  Host-only. */
 int evo_encoder_flops(const evo_encoder* e, int32_t batch, uint64_t* flops_out);
+
+/* Test query: how a call of `batch` images would run on an encoder of this
+ * description on a device of n_cu compute units.  For every convolution in
+ * execution order (stem; per block a, b and, where projected, d) out receives
+ * four numbers: workgroups, images per workgroup, 16-channel blocks per
+ * workgroup, K shares; zeros where the layer runs on the general path.
+ * Returns the number of convolutions, or a negative EVO_E_* code (n_out below
+ * four times that number: EVO_E_INVALID).  Host-only. */
+int evo_debug_encoder_plan(const evo_encoder_desc* desc, int32_t batch, int32_t n_cu, int32_t* out, int32_t n_out);
 
 /* Release the encoder (NULL is a no-op); synchronises its device first. */
 void evo_destroy_encoder(evo_encoder* e);

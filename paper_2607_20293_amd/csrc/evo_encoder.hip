@@ -732,8 +732,12 @@ __global__ void __launch_bounds__(kThreads) gn_fused_kernel(const GnArgs a) {
 // of 7 x 4 or 8 x 4 blocks needs about half of either.  A small batch takes
 // 16 channels a workgroup, for more workgroups and a shorter weight stream.
 // An image's results do not depend on its place in a tile, the other images
-// or the batch: rows of a product are independent and the statistics sum a
-// row's channels, then the rows of the image, in a fixed order.
+// or the arrangement, as long as WK is the same (and MBW and WM, where the
+// statistics are summed in registers): rows of a product are independent, an
+// element's products are summed in the order of K within a share, and the
+// statistics in an order that the map's size or the waves' rows decide.  So a
+// call of few images takes an arrangement of its own (see plan_layer) and
+// gives the same bits.
 constexpr int kPix = 144;  // LDS bytes of a pixel's 64 channels
 
 struct FusedArgs {
@@ -750,6 +754,8 @@ struct FusedArgs {
   int ipw, PW, PP, nit;  // images per workgroup, LDS row and image pixels, chunks per K share
   uint32_t div_px, div_pw, div_hw, div_wo, div_ipw;  // ceil(2^32 / d) of PP, PW, Ho * Wo, Wo, ipw (0: ipw is 1)
   int mt, nt, a_bytes;
+  int in_regs;  // GroupNorm statistics in registers (FusedPlan::in_regs)
+  int tpl;      // else log2 of the threads that sum the rows of one (group, image)
   float eps;
 };
 
@@ -769,8 +775,38 @@ __device__ __forceinline__ float quad_sum(float v) {  // over the lanes that sha
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// (The statistics follow the A region in LDS: one image, the waves' sums,
-// twice; several, row sums [channel blocks][rows], mean and 1 / deviation.)
+// sum over each 1 << lg consecutive lanes, in all of them (register moves:
+// a tree through LDS shuffles cost 0.4 us a sum)
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v) {
+  const u32x2 x = __builtin_bit_cast(u32x2, v);
+  const u32x2 y = {(unsigned)__builtin_amdgcn_mov_dpp((int)x[0], CTRL, 0xF, 0xF, true),
+                   (unsigned)__builtin_amdgcn_mov_dpp((int)x[1], CTRL, 0xF, 0xF, true)};
+  return v + __builtin_bit_cast(double, y);
+}
+__device__ __forceinline__ double lanes_sum(double v, int lg) {
+  if (lg > 0) v = add_dpp<0xB1>(v);   // neighbours
+  if (lg > 1) v = add_dpp<0x4E>(v);   // pairs
+  if (lg > 2) v = add_dpp<0x141>(v);  // quads
+  if (lg > 3) v = add_dpp<0x140>(v);  // halves of a row of 16
+  if (lg > 4) {
+    const u32x2 x = __builtin_bit_cast(u32x2, v);
+    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(x[0], x[0], false, false));
+    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(x[1], x[1], false, false));
+    v = __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+  }
+  if (lg > 5) {
+    const u32x2 x = __builtin_bit_cast(u32x2, v);
+    const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(x[0], x[0], false, false));
+    const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(x[1], x[1], false, false));
+    v = __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+  }
+  return v;
+}
+
+// (LDS: the A region, which the row sums [channel blocks][rows] of the
+// statistics take over; then their mean and 1 / deviation [channel blocks]
+// [ipw], or summed in registers the waves' sums, twice.)
 template <int MBW, int NBW, int WM, int WN, int WK, int TAPS>
 __global__ void __launch_bounds__(WM * WN * WK * 64, MBW * NBW > 32 ? 1 : 2) conv_gn_kernel(const FusedArgs a) {
   constexpr int NT = WM * WN * WK * 64, NB = NBW * WN, S = TAPS * 2;
@@ -909,19 +945,20 @@ __global__ void __launch_bounds__(WM * WN * WK * 64, MBW * NBW > 32 ? 1 : 2) con
   }
 
   // ---- GroupNorm statistics of every image and group (mean, then the
-  // squares around it).  One image a workgroup: a lane's rows, the wave's
-  // lanes, then the waves in order.  Several: the channels of each row to
-  // LDS, then the rows of an image.
-  float* const rsum = reinterpret_cast<float*>(lds + a.a_bytes);
+  // squares around it).  In registers (one image a workgroup, also in the
+  // max_batch arrangement): a lane's rows, the wave's lanes, then the waves in order.  Else the channels
+  // of each row to LDS, 1 << tpl threads take every (1 << tpl)-th row of an
+  // image, and a tree adds the threads.
+  float* const smean = reinterpret_cast<float*>(lds + a.a_bytes);  // [NB][ipw]
+  float* const srstd = smean + NB * a.ipw;
   const double inv_cnt = 1.0 / ((double)HW * 16.0);
   const auto row_of = [&](int m) { return (wm * MBW + m) * 16 + lc; };
   float mu[NBW], rs[NBW];  // one image; several: in LDS
-  float* const smean = rsum + NB * rows;  // [NB][ipw]
-  float* const srstd = smean + NB * a.ipw;
   int im[MBW];
 #pragma unroll
   for (int m = 0; m < MBW; ++m) im[m] = a.ipw > 1 ? fast_div(min(row_of(m), rows - 1), a.div_hw) : 0;
-  if (a.ipw == 1) {
+  if (a.in_regs) {
+    float* const buf = smean;  // [2][NW][NB]
     constexpr int NW = WM * WK;
     const auto total = [&](float* buf, auto value, double (&out)[NBW]) {  // buf [NW][NB]
 #pragma unroll
@@ -946,19 +983,18 @@ __global__ void __launch_bounds__(WM * WN * WK * 64, MBW * NBW > 32 ? 1 : 2) con
       }
     };
     double t[NBW];
-    total(rsum, [&](int m, int n) { return (acc[m][n][0] + acc[m][n][1]) + (acc[m][n][2] + acc[m][n][3]); }, t);
+    total(buf, [&](int m, int n) { return (acc[m][n][0] + acc[m][n][1]) + (acc[m][n][2] + acc[m][n][3]); }, t);
 #pragma unroll
     for (int n = 0; n < NBW; ++n) mu[n] = (float)(t[n] * inv_cnt);
-    total(rsum + NW * NB, [&](int m, int n) {
+    total(buf + NW * NB, [&](int m, int n) {
       const f32x4 d = acc[m][n] - mu[n];
       return (d[0] * d[0] + d[1] * d[1]) + (d[2] * d[2] + d[3] * d[3]);
     }, t);
 #pragma unroll
     for (int n = 0; n < NBW; ++n) rs[n] = (float)(1.0 / std::sqrt(t[n] * inv_cnt + (double)a.eps));
   } else {
-    const int pairs = NB * a.ipw;
-    int tp = 64;                         // threads per (group, image): rows l, l + tp, ..., then a tree
-    while (tp > 1 && tp * pairs > NT) tp >>= 1;
+    float* const rsum = reinterpret_cast<float*>(lds);  // [NB][rows], in the A region's place
+    const int pairs = NB * a.ipw, tp = 1 << a.tpl;
     const auto total = [&](auto value, auto finish, float* st) {
 #pragma unroll
       for (int m = 0; m < MBW; ++m)
@@ -972,14 +1008,20 @@ __global__ void __launch_bounds__(WM * WN * WK * 64, MBW * NBW > 32 ? 1 : 2) con
           }
         }
       __syncthreads();
-      for (int p0 = 0; p0 < pairs; p0 += NT / tp) {
-        const int p = p0 + tid / tp, l = tid % tp, nb = fast_div(p, a.div_ipw);
+      for (int p0 = 0; p0 < pairs; p0 += NT >> a.tpl) {
+        const int p = p0 + (tid >> a.tpl), l = tid & (tp - 1), nb = a.div_ipw ? fast_div(p, a.div_ipw) : p;
         double sum = 0.0;
         if (p < pairs) {
           const float* src = rsum + nb * rows + (p - nb * a.ipw) * HW;
-          for (int r = l; r < HW; r += tp) sum += (double)src[r];
+          for (int r = l; r < HW; r += 8 * tp) {  // eight reads in flight
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = src[min(r + k * tp, HW - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sum += r + k * tp < HW ? (double)v[k] : 0.0;
+          }
         }
-        for (int h = tp >> 1; h > 0; h >>= 1) sum += __shfl_xor(sum, h);
+        sum = lanes_sum(sum, a.tpl);
         if (p < pairs && l == 0) st[p] = finish(sum);
       }
       __syncthreads();
@@ -1023,7 +1065,7 @@ __global__ void __launch_bounds__(WM * WN * WK * 64, MBW * NBW > 32 ? 1 : 2) con
 #pragma unroll
       for (int n = 0; n < NBW; ++n) {
         const int q = (wn * NBW + n) * a.ipw + im[m];
-        const float mn = a.ipw == 1 ? mu[n] : smean[q], rd = a.ipw == 1 ? rs[n] : srstd[q];
+        const float mn = a.in_regs ? mu[n] : smean[q], rd = a.in_regs ? rs[n] : srstd[q];
         f32x4 v = (acc[m][n] - mn) * rd * gm[n] + bt[n];
         if (a.res) v += res[m & 1][n];
         if (a.relu) {
@@ -1063,12 +1105,19 @@ __global__ void pack_fused_kernel(const float* __restrict__ w, int Cout, int Cin
   }
 }
 
-// compiled wave arrangements (MBW, NBW, WM, WN, WK)
+// compiled wave arrangements (MBW, NBW, WM, WN, WK).  The last seven are taken
+// only by small calls of encoders whose layer runs a wide one with the same
+// rows (free to choose, more waves of fewer rows are faster: 2 frames of
+// 84x84, first stage, 9.5 us a layer with (4, 1, 8, 1, 1) against 12.0 with
+// (7, 1, 4, 1, 1)).
 #define EVO_FUSED(X)                                                                              \
   X(7, 4, 4, 1, 1) X(9, 4, 4, 1, 1) X(4, 4, 2, 2, 1) X(8, 4, 1, 2, 2) X(9, 4, 1, 2, 2)            \
   X(5, 4, 1, 2, 2) X(5, 4, 1, 1, 4) X(4, 1, 8, 1, 1) X(5, 1, 8, 1, 1) X(2, 1, 4, 1, 2)            \
   X(3, 1, 4, 1, 2) X(2, 1, 4, 1, 1) X(3, 1, 4, 1, 1) X(3, 1, 1, 1, 4) X(3, 1, 1, 1, 2)            \
-  X(1, 1, 1, 1, 8) X(1, 1, 1, 1, 4) X(3, 2, 1, 2, 4) X(3, 2, 1, 2, 2) X(5, 2, 1, 2, 2)
+  X(1, 1, 1, 1, 8) X(1, 1, 1, 1, 4) X(3, 2, 1, 2, 4) X(3, 2, 1, 2, 2) X(5, 2, 1, 2, 2)            \
+  X(7, 1, 4, 1, 1) X(9, 1, 4, 1, 1) X(4, 1, 2, 1, 1) X(8, 1, 1, 1, 2) X(9, 1, 1, 1, 2)            \
+  X(5, 1, 1, 1, 2) X(5, 1, 1, 1, 4)
+constexpr int kSmallCalls = 7;
 
 struct FusedCfg {
   int mbw, nbw, wm, wn, wk;
@@ -1094,6 +1143,7 @@ constexpr size_t kLdsBytes = 160 * 1024;
 // 2 ow + 2 (lane / 16) of the row.  The 7 x NB weight fragments stay in
 // registers.  512 frames of 84x84: three kernels 282 us, this one 107 us.
 constexpr int kStemWaves = 8, kStripRows = 5;
+constexpr int kStemWide = 128;  // images from which a workgroup takes all 64 channels
 
 struct StemArgs {
   const float* x;    // [N][H][W][Cin]
@@ -1274,15 +1324,23 @@ __global__ void pack_conv_kernel(const float* __restrict__ w, int Cout, int K, i
 
 unsigned grid_for(long long total) { return (unsigned)std::min<long long>((total + 255) / 256, 16384); }
 
-// A fused layer's launch, chosen at creation for the encoder's max_batch.
+// A fused layer's launch.
 struct FusedPlan {
   int cfg = -1, ipw = 0, PW = 0, PP = 0, nit = 0, a_bytes = 0, lds = 0;
+  bool in_regs = false;
 };
+// Plans are made at creation, one for every power of two of images a call may
+// have (the last one for max_batch): plan plan_class(n) serves n images.
+int plan_class(int n) {
+  int c = 0;
+  while ((1 << c) < n) ++c;
+  return c;
+}
 
 struct ConvLayer {
   int cin, cout, k, stride, pad, K, Kp;
   void* w = nullptr;             // packed operand weights
-  FusedPlan fp;
+  std::vector<FusedPlan> fp;     // [plan_class(max_batch) + 1]
   const float* gamma = nullptr;  // GroupNorm affine (device, inside the raw copy)
   const float* beta = nullptr;
 };
@@ -1294,7 +1352,7 @@ struct evo_encoder {
   int device = 0;
   int bf = 1;
   bool fused = false;            // the layers after the stem run as conv_gn_kernel
-  int stem_nb = 0;               // 16-channel blocks a workgroup of stem_kernel takes (0: the stem runs unfused)
+  int stem_nb = 0;               // 16-channel blocks a workgroup of stem_kernel takes in large calls (0: the stem runs unfused)
   float* d_raw = nullptr;        // fp32 parameter copy (GroupNorm affine, packing source)
   std::vector<ConvLayer> convs;  // stem, then per block a, b[, d]
   float* buf[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -1376,30 +1434,34 @@ ConvPlan plan_conv(int M, int Cout, int steps) {
   return pl;
 }
 
-// Cheapest wave arrangement of a fused layer on an H x W input.  Cycles of a
-// workgroup: matrix cores, its weight stream from L2 (48 bytes a cycle and
+// Cheapest wave arrangement of a fused layer for n images of H x W, with the
+// order of sums of `like` if given.  Cycles of a workgroup: matrix cores, its weight stream from L2 (48 bytes a cycle and
 // CU), its LDS reads, each shared by the workgroups that run on a CU at once;
 // plus staging and about 5000 for its start and statistics.
-bool plan_fused(int max_batch, const ConvLayer& L, int H, int W, bool pool, int n_cu, FusedPlan* out) {
+bool plan_fused(int n, const ConvLayer& L, int H, int W, bool pool, int n_cu, const FusedPlan* like, FusedPlan* out) {
   const int Ho = out_size(H, L.k, L.stride, L.pad), Wo = out_size(W, L.k, L.stride, L.pad), HW = Ho * Wo;
   if ((L.k != 3 && L.k != 1) || L.cin % 64 || L.cout % 64 || Wo < 2 || HW < 2) return false;
   const int nch = L.cin / 64, S = L.k * L.k * 2;
   const int PW = L.k == 1 ? Wo : W + 1, PP = L.k == 1 ? HW : (H + 2) * PW + 1;
   double best = 0.0;
   out->cfg = -1;
-  for (int c = 0; c < (int)(sizeof(kFused) / sizeof(kFused[0])); ++c) {
+  for (int c = 0; c < (int)(sizeof(kFused) / sizeof(kFused[0])) - (like ? 0 : kSmallCalls); ++c) {
     const FusedCfg& f = kFused[c];
     const int nb = f.nbw * f.wn, cap = 16 * f.mbw * f.wm, waves = f.wm * f.wn * f.wk;
     if (L.cout % (16 * nb) || nch % f.wk || cap < HW) continue;
-    for (int ipw = 1; ipw <= std::min(cap / HW, max_batch); ++ipw) {
+    if (like && f.wk != kFused[like->cfg].wk) continue;
+    if (like && like->in_regs && (f.mbw != kFused[like->cfg].mbw || f.wm != kFused[like->cfg].wm)) continue;
+    for (int ipw = 1; ipw <= (like && like->in_regs ? 1 : std::min(cap / HW, n)); ++ipw) {
       const int rows = ipw * HW;
       const long long stage = (long long)f.wk * ipw * PP * kPix;
       const long long part = (long long)(f.wk - 1) * f.wm * f.wn * f.mbw * f.nbw * 1024;
-      const long long a_bytes = (std::max({stage, part, pool ? (long long)rows * 16 * nb * 4 : 0ll}) + 15) / 16 * 16;
-      const long long lds = a_bytes + (ipw == 1 ? 2ll * f.wm * f.wk * nb * 4 : (long long)nb * (rows + 2 * ipw) * 4);
+      const bool in_regs = like ? like->in_regs : ipw == 1;
+      const long long stats = in_regs ? 0 : (long long)rows * nb * 4;
+      const long long a_bytes = (std::max({stage, part, pool ? (long long)rows * 16 * nb * 4 : 0ll, stats}) + 15) / 16 * 16;
+      const long long lds = a_bytes + 2ll * nb * (in_regs ? f.wm * f.wk : ipw) * 4;
       if (lds > (long long)kLdsBytes) continue;
       const int nit = nch / f.wk;
-      const long long wgs = (long long)cdiv(max_batch, ipw) * (L.cout / (16 * nb));
+      const long long wgs = (long long)cdiv(n, ipw) * (L.cout / (16 * nb));
       const long long occ = std::max(1ll, std::min((long long)kLdsBytes / lds, 8ll / waves));
       const double on = (double)std::min<long long>(occ, (wgs + n_cu - 1) / n_cu);  // workgroups that share a CU
       const double steps = (double)nit * S, one = f.mbw * f.nbw * 16.0 * steps;      // one wave's MFMAs
@@ -1408,11 +1470,31 @@ bool plan_fused(int max_batch, const ConvLayer& L, int H, int W, bool pool, int 
       const double cost = (double)((wgs + n_cu * occ - 1) / (n_cu * occ)) * (std::max({mf, l2, ld}) + st + 5000.0);
       if (out->cfg < 0 || cost < best) {
         best = cost;
-        *out = FusedPlan{c, ipw, PW, PP, nit, (int)a_bytes, (int)lds};
+        *out = FusedPlan{c, ipw, PW, PP, nit, (int)a_bytes, (int)lds, in_regs};
       }
     }
   }
   return out->cfg >= 0;
+}
+
+// The plans of a layer: the best arrangement for max_batch, which decides the
+// order of every sum (see conv_gn_kernel), and for every smaller class of
+// calls the best one with that order.
+bool plan_layer(int max_batch, ConvLayer& L, int H, int W, bool pool, int n_cu) {
+  const int last = plan_class(max_batch);
+  L.fp.assign(last + 1, FusedPlan());
+  // A map too large for arrangements with K shares, five or more 64-channel
+  // chunks one after another and too few images to fill the device: the
+  // general path's K splits are faster (96x96 frames, widths 320 and 640 or
+  // 512 to 2048: 210 and 192 us against 269 and 264 for one frame, 233 and 237
+  // against 271 and 268 for two; from 16 frames with widths 512 to 2048 667
+  // against 599)
+  const int Ho = out_size(H, L.k, L.stride, L.pad), Wo = out_size(W, L.k, L.stride, L.pad);
+  if (Ho * Wo > 144 && L.cin >= 320 && L.k == 3 && max_batch < 4) return false;
+  if (!plan_fused(max_batch, L, H, W, pool, n_cu, nullptr, &L.fp[last])) return false;
+  for (int c = 0; c < last; ++c)
+    if (!plan_fused(1 << c, L, H, W, pool, n_cu, &L.fp[last], &L.fp[c])) return false;
+  return true;
 }
 
 const void* fused_kernel(int cfg, int k) {
@@ -1429,7 +1511,7 @@ const void* fused_kernel(int cfg, int k) {
 // One fused layer on N images of H x W (`*Ho` x `*Wo` out).
 hipError_t launch_fused(const ConvLayer& L, const __bf16* x, int N, int H, int W, int* Ho, int* Wo, const float* res,
                         int relu, float* yf, __bf16* yb, float* feat, int out_stride, hipStream_t st) {
-  const FusedPlan& p = L.fp;
+  const FusedPlan& p = L.fp[plan_class(N)];
   const FusedCfg& f = kFused[p.cfg];
   const auto magic = [](int d) { return (uint32_t)(((uint64_t(1) << 32) + d - 1) / d); };
   FusedArgs a;
@@ -1463,6 +1545,9 @@ hipError_t launch_fused(const ConvLayer& L, const __bf16* x, int N, int H, int W
   a.mt = cdiv(N, p.ipw);
   a.nt = L.cout / (16 * f.nbw * f.wn);
   a.a_bytes = p.a_bytes;
+  a.in_regs = p.in_regs;
+  a.tpl = 0;  // about eight rows a thread
+  while (a.tpl < 6 && (8 << a.tpl) < a.Ho * a.Wo) ++a.tpl;
   a.eps = 1e-5f;
   void* args[] = {&a};
   return hipLaunchKernel(fused_kernel(p.cfg, L.k), dim3((unsigned)(a.mt * a.nt)), dim3(f.wm * f.wn * f.wk * 64), args,
@@ -1489,7 +1574,10 @@ hipError_t launch_stem(const evo_encoder* e, const ConvLayer& L, const float* im
   const evo_encoder_desc& d = e->desc;
   const auto magic = [](int v) { return (uint32_t)(((uint64_t(1) << 32) + v - 1) / v); };
   StemArgs a;
-  const int lds = stem_lds(d, e->stem_nb, &a.strip_off, &a.red_off);
+  // all channels a workgroup where the images alone fill the device, else one
+  // group (more workgroups, each with the whole image; the same bits)
+  const int nb = N >= kStemWide ? e->stem_nb : 1;
+  const int lds = stem_lds(d, nb, &a.strip_off, &a.red_off);
   a.x = images;
   a.w = reinterpret_cast<const uint4*>(L.w);
   a.gamma = L.gamma;
@@ -1506,13 +1594,41 @@ hipError_t launch_stem(const evo_encoder* e, const ConvLayer& L, const float* im
   a.C = L.cout;
   a.PW = stem_pitch(d.width);
   a.PR = 2 * (a.Ho - 1) + 7;
-  a.nt = L.cout / (16 * e->stem_nb);
+  a.nt = L.cout / (16 * nb);
   a.div_pw = magic(a.PW);
   a.div_wo = magic(a.Wo);
   a.div_wp = magic(a.Wp);
   a.eps = 1e-5f;
   void* args[] = {&a};
-  return hipLaunchKernel(stem_fn(e->stem_nb), dim3((unsigned)(N * a.nt)), dim3(kStemWaves * 64), args, (size_t)lds, st);
+  return hipLaunchKernel(stem_fn(nb), dim3((unsigned)(N * a.nt)), dim3(kStemWaves * 64), args, (size_t)lds, st);
+}
+
+// Which layers run fused, and their plans.  Every layer after the stem, or
+// none (see conv_gn_kernel): bf16 operands, groups of 16 channels, and an
+// arrangement for every layer.  The stem too where the image fits LDS.
+void plan_encoder(evo_encoder* e, int n_cu) {
+  const evo_encoder_desc& d = e->desc;
+  e->fused = e->bf && d.gn_group == 16;
+  int h = out_size(out_size(d.height, 7, 2, 3), 3, 2, 1), w = out_size(out_size(d.width, 7, 2, 3), 3, 2, 1);
+  size_t i = 1;
+  int cin = d.stem_ch;
+  for (int s = 0; s < d.n_stages && e->fused; ++s)
+    for (int b = 0; b < d.blocks[s] && e->fused; ++b) {
+      ConvLayer& La = e->convs[i++];
+      ConvLayer& Lb = e->convs[i++];
+      const int ho = out_size(h, 3, La.stride, 1), wo = out_size(w, 3, La.stride, 1);
+      const bool last = s == d.n_stages - 1 && b == d.blocks[s] - 1;
+      e->fused = plan_layer(d.max_batch, La, h, w, false, n_cu) && plan_layer(d.max_batch, Lb, ho, wo, last, n_cu) &&
+                 ((La.stride == 1 && cin == Lb.cout) || plan_layer(d.max_batch, e->convs[i++], h, w, false, n_cu));
+      h = ho;
+      w = wo;
+      cin = Lb.cout;
+    }
+  if (e->fused && d.in_ch <= 4 && d.width >= 12 && d.stem_ch % 64 == 0) {
+    int so, ro;
+    const int nb = d.max_batch >= kStemWide ? 4 : 1;
+    if (stem_lds(d, nb, &so, &ro)) e->stem_nb = nb;
+  }
 }
 
 // The conv result lands in `y` (one split) or as partials in the encoder's
@@ -1683,43 +1799,10 @@ int evo_create_encoder(const evo_encoder_desc* desc, const float* host_weights, 
     ENC_TRY(hipMalloc(&e->d_raw, n_floats * sizeof(float)));
     ENC_TRY(hipMemcpy(e->d_raw, host_weights, n_floats * sizeof(float), hipMemcpyHostToDevice));
     e->convs = enc_layers(desc);
-    // every layer after the stem fused, or none (see conv_gn_kernel): bf16
-    // operands, groups of 16 channels, and an arrangement for every layer
-    // (84x84 frames, fused and general path: 2 frames 171 and 259 us, 100
-    // frames 397 and 519 us, 512 frames 755 and 1490 us)
-    e->fused = e->bf && desc->gn_group == 16;
-    {
-      int n_cu = 256;
-      hipDeviceProp_t prop;
-      if (hipGetDeviceProperties(&prop, e->device) == hipSuccess) n_cu = prop.multiProcessorCount;
-      int h = out_size(out_size(desc->height, 7, 2, 3), 3, 2, 1), w = out_size(out_size(desc->width, 7, 2, 3), 3, 2, 1);
-      size_t i = 1;
-      int cin = desc->stem_ch;
-      for (int s = 0; s < desc->n_stages; ++s)
-        for (int b = 0; b < desc->blocks[s]; ++b) {
-          ConvLayer& La = e->convs[i++];
-          ConvLayer& Lb = e->convs[i++];
-          const int ho = out_size(h, 3, La.stride, 1), wo = out_size(w, 3, La.stride, 1);
-          e->fused = e->fused && plan_fused(desc->max_batch, La, h, w, false, n_cu, &La.fp) &&
-                     plan_fused(desc->max_batch, Lb, ho, wo,
-                                s == desc->n_stages - 1 && b == desc->blocks[s] - 1, n_cu, &Lb.fp);
-          if (La.stride != 1 || cin != Lb.cout) {
-            ConvLayer& Ld = e->convs[i++];
-            e->fused = e->fused && plan_fused(desc->max_batch, Ld, h, w, false, n_cu, &Ld.fp);
-          }
-          h = ho;
-          w = wo;
-          cin = Lb.cout;
-        }
-    }
-    // the stem fused too where the image fits LDS: all channels a workgroup
-    // where the images alone fill the device, else one group (more
-    // workgroups, each with the whole image)
-    if (e->fused && desc->in_ch <= 4 && desc->width >= 12 && desc->stem_ch % 64 == 0) {
-      int so, ro;
-      const int nb = desc->max_batch >= 128 ? 4 : 1;
-      if (stem_lds(*desc, nb, &so, &ro)) e->stem_nb = nb;
-    }
+    int n_cu = 256;
+    hipDeviceProp_t prop;
+    if (hipGetDeviceProperties(&prop, e->device) == hipSuccess) n_cu = prop.multiProcessorCount;
+    plan_encoder(e, n_cu);
     const int KS = e->bf ? ConvStep<__bf16>::KS : ConvStep<float>::KS;
     size_t off = 0;
     for (ConvLayer& L : e->convs) {
@@ -1730,11 +1813,13 @@ int evo_create_encoder(const evo_encoder_desc* desc, const float* host_weights, 
       if (e->fused && L.k != 7) {
         hipLaunchKernelGGL(pack_fused_kernel, dim3(grid_for((long long)L.cout * L.K / 8)), dim3(256), 0, 0, e->d_raw + off,
                            L.cout, L.cin, L.k * L.k, reinterpret_cast<uint4*>(L.w));
-        ENC_TRY(hipFuncSetAttribute(fused_kernel(L.fp.cfg, L.k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
+        for (const FusedPlan& p : L.fp)
+          ENC_TRY(hipFuncSetAttribute(fused_kernel(p.cfg, L.k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
       } else if (e->stem_nb && L.k == 7) {
         hipLaunchKernelGGL(pack_stem_kernel, dim3(grid_for(7ll * L.cout * 4)), dim3(256), 0, 0, e->d_raw + off, L.cout, L.cin,
                            reinterpret_cast<uint4*>(L.w));
-        ENC_TRY(hipFuncSetAttribute(stem_fn(e->stem_nb), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
+        for (int nb : {1, e->stem_nb})
+          ENC_TRY(hipFuncSetAttribute(stem_fn(nb), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
       } else
         hipLaunchKernelGGL(pack_conv_kernel, dim3(grid_for((long long)L.cout * L.Kp)), dim3(256), 0, 0,
                          e->d_raw + off, L.cout, L.K, L.Kp, e->bf, L.w);
@@ -1759,6 +1844,36 @@ int evo_create_encoder(const evo_encoder_desc* desc, const float* host_weights, 
   rc = guarded(body);
   if (rc) evo_destroy_encoder(e);
   return rc;
+}
+
+int evo_debug_encoder_plan(const evo_encoder_desc* desc, int32_t batch, int32_t n_cu, int32_t* out, int32_t n_out) {
+  clear_error();
+  int rc = enc_check(desc);
+  if (rc) return rc;
+  if (batch < 1 || batch > desc->max_batch || n_cu < 1 || !out) return fail(EVO_E_INVALID, "bad argument");
+  return guarded([&]() -> int {
+    evo_encoder e;
+    e.desc = *desc;
+    e.bf = desc->dtype == EVO_BF16;
+    e.convs = enc_layers(desc);
+    if (n_out < (int)(4 * e.convs.size())) return fail(EVO_E_INVALID, "n_out %d < %zu", n_out, 4 * e.convs.size());
+    plan_encoder(&e, n_cu);
+    for (size_t i = 0; i < e.convs.size(); ++i) {
+      int32_t* o = out + 4 * i;
+      const ConvLayer& L = e.convs[i];
+      std::fill(o, o + 4, 0);
+      if (i == 0 && e.stem_nb) {
+        const int nb = batch >= kStemWide ? e.stem_nb : 1;
+        o[0] = batch * (L.cout / (16 * nb)), o[1] = 1, o[2] = nb, o[3] = 1;
+      } else if (i > 0 && e.fused) {
+        const FusedPlan& p = L.fp[plan_class(batch)];
+        const FusedCfg& f = kFused[p.cfg];
+        o[1] = p.ipw, o[2] = f.nbw * f.wn, o[3] = f.wk;
+        o[0] = cdiv(batch, p.ipw) * (L.cout / (16 * o[2]));
+      }
+    }
+    return (int)e.convs.size();
+  });
 }
 
 int evo_encode(evo_encoder* e, int32_t batch, const float* images, float* features_out, int32_t out_stride,

@@ -28,7 +28,7 @@ EXPORTED = ("evo_weight_count", "evo_check_desc", "evo_create_policy", "evo_set_
             "evo_guided_sample", "evo_ga_initial_population", "evo_ga_next_generation", "evo_ga_search",
             "evo_search", "evo_encoder_weight_count", "evo_create_encoder", "evo_encode", "evo_encoder_flops",
             "evo_destroy_encoder", "evo_set_kernel_timing", "evo_kernel_time", "evo_denoise_noalloc",
-            "evo_noalloc_scratch_bytes")
+            "evo_noalloc_scratch_bytes", "evo_debug_encoder_plan")
 
 
 def guided_probabilities(scores, eps: float, gamma: float) -> np.ndarray:
@@ -262,6 +262,8 @@ def lib() -> ctypes.CDLL:
         L.evo_encode.restype = ctypes.c_int
         L.evo_encoder_flops.argtypes = [P, I32, ctypes.POINTER(U64)]
         L.evo_encoder_flops.restype = ctypes.c_int
+        L.evo_debug_encoder_plan.argtypes = [ctypes.POINTER(EncoderDesc), I32, I32, P, I32]
+        L.evo_debug_encoder_plan.restype = ctypes.c_int
         L.evo_destroy_encoder.argtypes = [P]
         L.evo_destroy_encoder.restype = None
         L.evo_last_error.argtypes = []
@@ -521,6 +523,20 @@ def encoder_weight_count(desc: EncoderDesc) -> int:
     if n < 0:
         _check(int(n))
     return int(n)
+
+
+def encoder_plan(e, dtype: str, max_batch: int, batch: int, n_cu: int = 256) -> np.ndarray:
+    """How a call of `batch` images would run on an encoder planned for
+    max_batch (host only): int32 [convolutions][4] of workgroups, images per
+    workgroup, 16-channel blocks per workgroup, K shares; zeros on the general
+    path."""
+    n = 1 + sum(3 * b for b in e.blocks)
+    out = np.zeros((n, 4), np.int32)
+    desc = make_encoder_desc(e, dtype, max_batch)
+    rc = lib().evo_debug_encoder_plan(ctypes.byref(desc), batch, n_cu, out.ctypes.data, out.size)
+    if rc < 0:
+        _check(rc)
+    return out[:rc]
 
 
 class Encoder:

@@ -286,3 +286,26 @@ def test_encoder_fused_layers(size, planned, batch):
     print(f"[gpu] encoder {size} planned for {planned}, batch {batch}: rel {_rel(got, want):.2e}", flush=True)
     assert _rel(got, want) <= 3e-2
     assert np.array_equal(got, rev[::-1]) and np.array_equal(got[-1], one[0])
+
+
+@pytest.mark.parametrize("size,widths,planned", [((84, 84), (64, 128, 256, 512), 512), ((96, 96), (64, 128, 256, 512), 200),
+                                                 ((40, 43), (64, 192, 320, 1024), 256), ((40, 40), (64,), 512)])
+def test_encoder_fused_calls_of_every_size(size, widths, planned):
+    """A fused encoder splits a call's work by the call's batch (several
+    arrangements of every layer, the stem on 16 or 64 channels a workgroup);
+    an image's features are bit for bit the same under all of them."""
+    torch = _torch()
+    from paper_2607_20293_amd import evo
+    e = I.EncoderShape(*size, widths=widths, blocks=(2,) * len(widths))
+    enc = evo.Encoder(e, I.make_encoder_weights(e, 51, "perturbed"), "bf16", max_batch=planned)
+    imgs = torch.from_numpy(I.make_images(e, 200, 51)).cuda()
+    want = enc.encode(imgs).cpu().numpy()
+    plans = set()
+    for n in (1, 2, 3, 7, 16, 33, 65, 129):
+        plan = evo.encoder_plan(e, "bf16", planned, n)
+        assert (plan[:, 0] > 0).all()
+        plans.add(plan[:, 1:].tobytes())
+        got = enc.encode(imgs[200 - n:].contiguous()).cpu().numpy()
+        assert np.array_equal(got, want[200 - n:]), n
+    assert len(plans) >= 2
+    enc.close()

@@ -255,6 +255,45 @@ def test_encoder_calls_reject_null_handles_without_a_device():
     assert out.value is None
 
 
+@pytest.mark.parametrize("size", [40, 84, 96])
+@pytest.mark.parametrize("widths", [(64,), (64, 128, 256, 512), (64, 192, 320, 1024)])
+def test_encoder_plan_follows_the_calls_batch(size, widths):
+    """A call of few images on an encoder made for many spreads its fused
+    layers over workgroups of its own, not over the few that the max_batch
+    arrangement would leave it, with as many K shares (the order of the sums)
+    as that arrangement."""
+    _lib_or_skip()
+    e = I.EncoderShape(size, size, widths=widths, blocks=(2,) * len(widths))
+    top = evo.encoder_plan(e, "bf16", 512, 512)
+    assert (top[:, 0] > 0).all()
+    for n in (1, 2, 3, 8, 17, 64, 100, 129, 511):
+        plan = evo.encoder_plan(e, "bf16", 512, n)
+        assert np.array_equal(plan[:, 3], top[:, 3])
+        assert (plan[:, 1] <= n).all() and (plan[:, 0] > 0).all()
+        # workgroups of the max_batch arrangement for n images
+        share = top[:, 0] // -(-512 // top[:, 1]) * -(-n // top[:, 1])
+        assert (plan[:, 0] >= share).all()
+        if n <= 8:
+            assert plan[:, 0].sum() >= 2 * share.sum(), n
+    assert not evo.encoder_plan(e, "fp32", 512, 1).any()
+
+
+def test_encoder_plan_keeps_the_general_path_where_it_is_faster():
+    """A wide network on large maps for one or two frames is not fused (the
+    general path splits K over workgroups there), for more frames it is; odd
+    groups, widths and maps stay on the general path."""
+    _lib_or_skip()
+    e = I.EncoderShape(96, 96, widths=(320, 640), blocks=(2, 2))
+    assert not evo.encoder_plan(e, "bf16", 2, 1)[1:].any()
+    assert evo.encoder_plan(e, "bf16", 4, 1)[:, 0].all()
+    for f in (I.EncoderShape(84, 84, gn_group=8), I.EncoderShape(84, 84, widths=(64, 128, 200, 512), gn_group=8),
+              I.EncoderShape(120, 120), I.EncoderShape(32, 32)):
+        assert not evo.encoder_plan(f, "bf16", 64, 64).any()
+    # in_ch beyond 4: an unfused stem before fused layers
+    plan = evo.encoder_plan(I.EncoderShape(84, 84, in_ch=6), "bf16", 64, 64)
+    assert not plan[0].any() and plan[1:, 0].all()
+
+
 def test_maximum_step_count():
     """The per-tile step masks live in LDS (341 entries of 3 x u64): with
     two-sample tiles, 170 steps fit and 171 are refused as unsupported."""
