@@ -161,16 +161,18 @@ def test_encode_then_denoise_matches_oracle_chain(dtype):
     compare(got, ref, dtype, f"encode+denoise {dtype}")
 
 
-@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-def test_encoder_large_tiles_sampled_frames(dtype):
-    """A batch large enough that no convolution splits K (thousands of
-    output tiles, ragged in channels nowhere and in pixels at the last
-    stage), checked on sampled frames: frames are independent, so the
-    oracle runs on those frames alone."""
+@pytest.mark.parametrize("dtype,group", [("fp32", 16), ("bf16", 8), ("bf16", 16)])
+def test_encoder_large_tiles_sampled_frames(dtype, group):
+    """A batch large enough that no convolution of the general path (fp32, or
+    bf16 with groups of 8) splits K (thousands of output tiles, ragged in
+    channels nowhere and in pixels at the last stage); with bf16 and groups of
+    16 the fused layers.  Checked on sampled frames: frames are independent, so
+    the oracle runs on those frames alone."""
     torch = _torch()
     from paper_2607_20293_amd import evo
-    e = I.EncoderShape(64, 64, stem_ch=64, widths=(128, 256), blocks=(1, 1), gn_group=16)
+    e = I.EncoderShape(64, 64, stem_ch=64, widths=(128, 256), blocks=(1, 1), gn_group=group)
     B, pick = 256, [0, 77, 255]
+    assert (evo.encoder_plan(e, dtype, B, B)[:, 0] > 0).all() == (dtype == "bf16" and group == 16)
     w = I.make_encoder_weights(e, 31, "perturbed")
     imgs = I.make_images(e, B, 31)
     enc = evo.Encoder(e, w, dtype, max_batch=B)
@@ -236,10 +238,10 @@ def test_image_policy_query_matches_oracle_chain():
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_encoder_bench_batch_sampled_frames(dtype):
     """The benchmark's encode: 512 frames of 84x84 (the image policy's 256
-    chunks x 2 observation steps) on an encoder planned for 512 frames, which
-    runs the stem's GroupNorm in two passes and every other GroupNorm as one
-    kernel over several groups per workgroup; frames spread over the batch
-    against the oracle on those frames alone."""
+    chunks x 2 observation steps) on an encoder planned for 512 frames.  fp32:
+    the stem's GroupNorm in two passes and every other GroupNorm as one kernel
+    over several groups per workgroup; bf16: every layer fused.  Frames spread
+    over the batch against the oracle on those frames alone."""
     torch = _torch()
     from paper_2607_20293_amd import evo
     e = I.ENC_ROBOMIMIC
@@ -260,7 +262,7 @@ def test_encoder_bench_batch_sampled_frames(dtype):
 
 @pytest.mark.parametrize("size,planned,batch", [((84, 84), 512, 7), ((96, 96), 512, 3), ((84, 84), 100, 9),
                                                 ((96, 96), 40, 5), ((84, 84), 1, 1), ((61, 40), 300, 6),
-                                                ((33, 97), 3, 3), ((12, 12), 64, 5)])
+                                                ((33, 97), 3, 3), ((12, 12), 64, 5), ((12, 21), 130, 130)])
 def test_encoder_fused_layers(size, planned, batch):
     """The fused stem and conv + GroupNorm layers (bf16, groups of 16, widths
     of 64 and more) under the plans of several max_batch values: whole and
@@ -268,13 +270,15 @@ def test_encoder_fused_layers(size, planned, batch):
     the images a workgroup takes), maps from 576 pixels to 2 x 2, odd and
     non-square sizes, 1x1 projections with and without a stride; against the
     oracle, and bit for bit the same for an image at another place of another
-    batch.  The bound is the bf16 encoder bar above (each of the 12
-    convolutions rounds its input to 8 bits: 12^1/2 * 2^-9 = 7e-3 of
-    independent errors, normwise)."""
+    batch.  The stem's narrowest image (12 pixels) has two stages.  The bound
+    is the bf16 encoder bar above (each of the up to 12 convolutions rounds its
+    input to 8 bits: 12^1/2 * 2^-9 = 7e-3 of independent errors, normwise)."""
     torch = _torch()
     from paper_2607_20293_amd import evo
-    e = I.EncoderShape(*size, in_ch=3, widths=(128, 64, 128, 256) if size == (12, 12) else (64, 128, 256, 512),
-                       blocks=(1, 2, 1, 1))
+    small = min(size) == 12
+    e = I.EncoderShape(*size, in_ch=3, widths=(128, 64) if small else (64, 128, 256, 512),
+                       blocks=(1, 2) if small else (1, 2, 1, 1))
+    assert (evo.encoder_plan(e, "bf16", planned, batch)[:, 0] > 0).all()
     w = I.make_encoder_weights(e, 31, "perturbed")
     imgs = I.make_images(e, batch, 31)
     enc = evo.Encoder(e, w, "bf16", max_batch=planned)
@@ -309,3 +313,23 @@ def test_encoder_fused_calls_of_every_size(size, widths, planned):
         assert np.array_equal(got, want[200 - n:]), n
     assert len(plans) >= 2
     enc.close()
+
+
+@pytest.mark.parametrize("size,in_ch,planned,batch", [(84, 6, 3, 3), (40, 5, 256, 4)])
+def test_encoder_unfused_stem_before_fused_layers(size, in_ch, planned, batch):
+    """More than 4 image channels: the general path's stem (its GroupNorm in
+    two passes for the 42 x 42 map, in one kernel for the 20 x 20 map) hands
+    its output to the fused layers in fp32 and rounded."""
+    torch = _torch()
+    from paper_2607_20293_amd import evo
+    e = I.EncoderShape(size, size, in_ch=in_ch, widths=(64, 128), blocks=(2, 1))
+    plan = evo.encoder_plan(e, "bf16", planned, batch)
+    assert plan[0, 0] == 0 and (plan[1:, 0] > 0).all()
+    w = I.make_encoder_weights(e, 52, "perturbed")
+    imgs = I.make_images(e, batch, 52)
+    enc = evo.Encoder(e, w, "bf16", max_batch=planned)
+    got = enc.encode(torch.from_numpy(imgs).cuda()).cpu().numpy()
+    enc.close()
+    want = E.encode(e, I.split_encoder_weights(e, w), imgs, "bf16")
+    print(f"[gpu] encoder {size} with {in_ch} channels: rel {_rel(got, want):.2e}", flush=True)
+    assert _rel(got, want) <= 3e-2
