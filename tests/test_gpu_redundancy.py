@@ -115,11 +115,12 @@ def test_scores_and_guided_schedule_end_to_end():
 
 
 @pytest.mark.parametrize("name,T,R", [("tiny", 2, 1), ("tiny", 16, 2), ("tiny", 17, 171), ("tiny", 128, 1),
-                                      ("pusht", 33, 1), ("pusht", 112, 2)])
+                                      ("pusht", 33, 1), ("pusht", 112, 2), ("tiny", 49, 90), ("tiny", 80, 90),
+                                      ("tiny", 96, 90), ("pusht", 49, 1), ("pusht", 80, 1), ("pusht", 96, 1)])
 def test_scores_at_tile_edges(name, T, R):
-    """Step counts at the edges of the 16-step tiles (every tile count has its
-    own kernel), few and many queries (the elements split over workgroups, or
-    not), on activations that drift from step to step, against fp64.  A score
+    """Step counts at the edges of the 16-step tiles and in every tile count from
+    1 to 8 (each has its own kernel), few and many queries (the elements split
+    over workgroups, or not), on activations that drift from step to step, against fp64.  A score
     is a mean of cosines, each a sum of V products in chains of at most V / 4
     fp32 additions, so it is within V / 4 * 2^-24 (plus rounding of the final
     steps) of the exact value."""
