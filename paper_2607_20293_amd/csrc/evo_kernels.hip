@@ -42,6 +42,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));  // in a caller's buffer (float alignment only)
 
 constexpr uint64_t kMergedBit = 1ull << 63;
 constexpr int kMaskEntries = 341;  // (T x samples per tile) entries of 3 x u64 in LDS (8 KiB)
@@ -1677,7 +1678,7 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
             h[c][rb] += v;
             if (p.acts != nullptr && member == 0) {
               // activation record of the uncached policy (Sec. 3.3): a[sample][unit][step][H][d]
-              *reinterpret_cast<f32x4*>(p.acts + (((size_t)smp[j] * U + e) * T + t) * (HZ * D) +
+              *reinterpret_cast<f32x4_dword*>(p.acts + (((size_t)smp[j] * U + e) * T + t) * (HZ * D) +
                                         (size_t)((rb * 16 + lc) % HZ) * D + (w * CBW + c) * 16 + lq * 4) = v;
             }
           } else if (pick(mru, j) & bit) {

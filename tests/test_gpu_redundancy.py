@@ -143,3 +143,26 @@ def test_scores_at_tile_edges(name, T, R):
     assert err <= tol
     assert np.array_equal(got, pol.redundancy_scores(dev_acts).cpu().numpy())  # fixed order of every sum
     pol.close()
+
+
+def test_activations_at_a_float_aligned_address():
+    """The caller's activation buffer needs the alignment of a float only, both
+    where it is recorded and where it is scored."""
+    import ctypes
+    import torch
+    s = I.TINY
+    dev = device()
+    pol, obs, noise, out, acts = _collect(s, I.make_weights(s, 26, "perturbed"), "fp32", 2, 26)
+    flat = torch.full((acts.numel() + 2,), 7.0, device=dev)
+    view = flat[1:-1]
+    assert view.data_ptr() % 16 == 4
+    o = torch.empty(out.shape, device=dev)
+    st = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    obs_d, noise_d = torch.from_numpy(obs).to(dev), torch.from_numpy(noise).to(dev)
+    assert evo.lib().evo_collect_activations(pol._h, 2, obs_d.data_ptr(), noise_d.data_ptr(), None, o.data_ptr(),
+                                             view.data_ptr(), st) == 0
+    pol.synchronize()
+    assert torch.equal(view.view_as(acts), acts) and np.array_equal(o.cpu().numpy(), out)
+    assert float(flat[0]) == 7.0 and float(flat[-1]) == 7.0
+    assert torch.equal(pol.redundancy_scores(view.view_as(acts)), pol.redundancy_scores(acts))
+    pol.close()
