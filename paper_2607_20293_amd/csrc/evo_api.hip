@@ -110,13 +110,11 @@ struct evo_policy {
   int n_cu = 256;
   WeightOffsets wo;
   std::vector<LayerOff> loff_h;
-  std::vector<PackOff> poff_h;
-  uint64_t pk_obs = 0, pk_win = 0, pk_wout = 0;
+  uint64_t pk_obs = 0, pk_win = 0, pk_wout = 0, pk_layers = 0;
   int obs_pad = 0;
   float* d_raw = nullptr;
   uint4* d_pk = nullptr;
   LayerOff* d_loff = nullptr;
-  PackOff* d_poff = nullptr;
   float* d_tkv = nullptr;
   float* d_tfold = nullptr;  // time-token fold records (folded cross-attention)
   float* d_ddpm = nullptr;
@@ -209,7 +207,6 @@ static void release(evo_policy* p) {
   (void)hipFree(p->d_raw);
   (void)hipFree(p->d_pk);
   (void)hipFree(p->d_loff);
-  (void)hipFree(p->d_poff);
   (void)hipFree(p->d_tkv);
   (void)hipFree(p->d_tfold);
   (void)hipFree(p->d_ddpm);
@@ -340,9 +337,13 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
     off += (uint64_t)(d / 16) * 1 * 64;
     p->pk_wout = off;
     off += (uint64_t)1 * (d / 16) * 64;
-    p->poff_h.resize(L);
+    struct PackOff {
+      uint64_t qkv, o, q, kv, o2, w1, w2;
+    };
+    std::vector<PackOff> pack(L);
+    p->pk_layers = off;
     for (int l = 0; l < L; ++l) {
-      PackOff& po = p->poff_h[l];
+      PackOff& po = pack[l];
       po.qkv = off; off += frag16(3 * d, d);
       po.o = off; off += frag16(d, d);
       po.q = off; off += frag16(d, d);
@@ -350,7 +351,27 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
       po.o2 = off; off += frag16(d, d);
       po.w1 = off; off += frag16(s.dff, d);
       po.w2 = off; off += frag16(d, s.dff);
-      po.pad_ = 0;
+    }
+    // the kernel addresses the layers at compile-time offsets: they must be these
+    for (int spt : {1, 2}) {
+      LayerLayout want;
+      if (!kernel_layer_layout(KernelKey{d, s.dh(), s.H, s.dff, s.dtype, spt, 1}, &want)) continue;
+      for (int l = 0; l < L; ++l) {
+        const auto& y = wo.layer[l];
+        const PackOff& po = pack[l];
+        const size_t at[13] = {y.ln1_g, y.ln1_b, y.b_qkv, y.b_o, y.ln2_g, y.ln2_b, y.b_q, y.b_o2, y.ln3_g, y.ln3_b, y.b_1, y.b_2,
+                               l + 1 < L ? wo.layer[l + 1].ln1_g : y.ln1_g + want.floats};
+        const uint64_t mat[7] = {po.qkv, po.o, po.q, po.o2, po.w1, po.w2, l + 1 < L ? pack[l + 1].qkv : off};
+        const size_t base = wo.layer[0].ln1_g + (size_t)l * want.floats;
+        const uint64_t pbase = p->pk_layers * 16 + (uint64_t)l * want.packed_bytes;
+        bool same = at[12] == base + want.floats && mat[6] * 16 == pbase + want.packed_bytes;
+        for (int i = 0; i < 12; ++i) same = same && at[i] == base + want.small[i];
+        for (int i = 0; i < 6; ++i) same = same && mat[i] * 16 == pbase + want.packed[i];
+        if (!same) {
+          release(p);
+          return fail(EVO_E_STATE, "the parameters of layer %d do not lie as the kernel is compiled for", l);
+        }
+      }
     }
     CREATE_TRY(hipMalloc(&p->d_pk, off * sizeof(uint4)));
     CREATE_TRY(launch_pack(p->d_raw, wo.W_obs, d, d, s.obs_dim, p->obs_pad, s.dtype, p->d_pk + p->pk_obs, 0));
@@ -358,7 +379,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
     CREATE_TRY(launch_pack(p->d_raw, wo.W_out, 16, s.A, d, d, EVO_FP32, p->d_pk + p->pk_wout, 0));
     for (int l = 0; l < L; ++l) {
       const auto& y = wo.layer[l];
-      const PackOff& po = p->poff_h[l];
+      const PackOff& po = pack[l];
       CREATE_TRY(launch_pack(p->d_raw, y.W_qkv, 3 * d, 3 * d, d, d, s.dtype, p->d_pk + po.qkv, 0));
       CREATE_TRY(launch_pack(p->d_raw, y.W_o, d, d, d, d, s.dtype, p->d_pk + po.o, 0));
       CREATE_TRY(launch_pack(p->d_raw, y.W_q, d, d, d, d, s.dtype, p->d_pk + po.q, 0));
@@ -367,27 +388,22 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
       CREATE_TRY(launch_pack(p->d_raw, y.W_1, s.dff, s.dff, d, d, s.dtype, p->d_pk + po.w1, 0));
       CREATE_TRY(launch_pack(p->d_raw, y.W_2, d, d, s.dff, s.dff, s.dtype, p->d_pk + po.w2, 0));
     }
-    // per-layer offsets of the small tensors
+    // per-layer offsets for the observation tokens' kernels
     p->loff_h.resize(L);
     std::vector<uint32_t> wkv(L), bkv(L);
     for (int l = 0; l < L; ++l) {
       const auto& y = wo.layer[l];
       LayerOff& lo = p->loff_h[l];
-      lo.ln1_g = (uint32_t)y.ln1_g; lo.ln1_b = (uint32_t)y.ln1_b; lo.b_qkv = (uint32_t)y.b_qkv;
-      lo.b_o = (uint32_t)y.b_o; lo.ln2_g = (uint32_t)y.ln2_g; lo.ln2_b = (uint32_t)y.ln2_b;
-      lo.b_q = (uint32_t)y.b_q; lo.b_kv = (uint32_t)y.b_kv; lo.b_o2 = (uint32_t)y.b_o2;
-      lo.ln3_g = (uint32_t)y.ln3_g; lo.ln3_b = (uint32_t)y.ln3_b; lo.b_1 = (uint32_t)y.b_1;
-      lo.b_2 = (uint32_t)y.b_2;
+      lo.b_q = (uint32_t)y.b_q;
+      lo.b_kv = (uint32_t)y.b_kv;
       lo.w_q = (uint32_t)y.W_q;
       lo.w_o2t = fold ? (uint32_t)(tr_off + (size_t)l * d * d) : 0u;
-      lo.pad_ = 0;
+      lo.pk_kv = pack[l].kv;
       wkv[l] = (uint32_t)y.W_kv;
       bkv[l] = (uint32_t)y.b_kv;
     }
     CREATE_TRY(hipMalloc(&p->d_loff, L * sizeof(LayerOff)));
     CREATE_TRY(hipMemcpy(p->d_loff, p->loff_h.data(), L * sizeof(LayerOff), hipMemcpyHostToDevice));
-    CREATE_TRY(hipMalloc(&p->d_poff, L * sizeof(PackOff)));
-    CREATE_TRY(hipMemcpy(p->d_poff, p->poff_h.data(), L * sizeof(PackOff), hipMemcpyHostToDevice));
 
     // time-token keys/values for every timestep and layer; sampler constants
     {
@@ -717,13 +733,13 @@ static int denoise_impl(evo_policy* p, int32_t batch, const float* obs_cond, con
     std::memset(&kp, 0, sizeof(kp));
     kp.L = s.L; kp.A = s.A; kp.n_obs = s.n_obs; kp.obs_dim = s.obs_dim; kp.obs_pad = p->obs_pad;
     kp.T = s.T; kp.clip = s.clip; kp.n_tiles = ps.n_tiles;
-    kp.raw = p->d_raw; kp.pk = p->d_pk; kp.loff = p->d_loff; kp.poff = p->d_poff; kp.pk_obs = p->pk_obs;
-    kp.pk_layers = p->poff_h[0].qkv;
+    kp.raw = p->d_raw; kp.pk = p->d_pk; kp.loff = p->d_loff; kp.pk_obs = p->pk_obs;
+    kp.pk_layers = p->pk_layers;
     kp.raw_layers = (uint32_t)p->wo.layer[0].ln1_g;
     const WeightOffsets& wo = p->wo;
-    kp.W_in = (uint32_t)wo.W_in; kp.b_in = (uint32_t)wo.b_in; kp.P_act = (uint32_t)wo.P_act;
+    kp.b_in = (uint32_t)wo.b_in; kp.P_act = (uint32_t)wo.P_act;
     kp.b_obs = (uint32_t)wo.b_obs; kp.P_mem = (uint32_t)wo.P_mem; kp.lnf_g = (uint32_t)wo.lnf_g;
-    kp.lnf_b = (uint32_t)wo.lnf_b; kp.W_out = (uint32_t)wo.W_out; kp.b_out = (uint32_t)wo.b_out;
+    kp.lnf_b = (uint32_t)wo.lnf_b; kp.b_out = (uint32_t)wo.b_out;
     kp.tkv = p->d_tkv; kp.ddpm = p->d_ddpm;
     kp.fold = fold ? 1 : 0;
     kp.tfold = p->d_tfold;
@@ -735,7 +751,6 @@ static int denoise_impl(evo_policy* p, int32_t batch, const float* obs_cond, con
     kp.obs = obs_cond; kp.noise = noise; kp.out = actions_out; kp.okv = cb.okv; kp.cache = cb.cache;
     kp.acts = acts_out;
     kp.batch = batch;
-    kp.team = team;
     kp.okv_member_stride = fold ? 0 : cb.okv_stride;  // fold records: one copy read by every team member
     if (team > 1) {
       kp.xchg = cb.xchg;

@@ -177,56 +177,26 @@ template <> struct Op<float> {
   }
 };
 
-// k-steps a product keeps in flight: about INFL 1 KiB fragments per wave
-template <int MPW, int NKF, int INFL>
-constexpr int pd_of() {
-  constexpr int pd0 = INFL / MPW > 0 ? INFL / MPW : 1;
-  return pd0 < NKF ? pd0 : (NKF > 1 ? NKF - 1 : 1);
-}
-// k-steps requested ahead of a product (before the phase that precedes it):
-// about PF fragments per wave, at least one k-step, at most the in-flight depth
-template <int MPW, int NKF, int INFL, int PF>
-constexpr int np_of() {
-  constexpr int n = PF / MPW > 0 ? PF / MPW : 1;
-  constexpr int pd = pd_of<MPW, NKF, INFL>();
-  return n < pd ? n : pd;
-}
-
-// First NP k-steps of weight fragments of a product (issued ahead of it).
-template <int NP, int MPW, class GCB>
-__device__ __forceinline__ void gemm_pref(uint4 (&bc)[NP][MPW], const uint4* W, int KBT, int kf0, GCB gcb,
-                                          int lane) {
-#pragma unroll
-  for (int d = 0; d < NP; ++d)
-#pragma unroll
-    for (int m = 0; m < MPW; ++m) bc[d][m] = W[((size_t)gcb(m) * KBT + kf0 + d) * 64 + lane];
-}
-
 // acc[m][rb] += (A[rb*16 .. +16][k-range] x W[col block gcb(m)][k-range]^T)^T
 // A: LDS operand, row stride lda elements, offset to the k-range start.
 // W: packed fragments of a matrix with KBT fragments per column block; kf0
-// is the first fragment of the k-range, NKF its length; bc holds the
-// fragments of the first NP k-steps (gemm_pref).  Weight fragments are
-// requested PD k-steps ahead of their MFMAs (about INFL 1 KiB fragments in
+// is the first fragment of the k-range, NKF its length.  Weight fragments are
+// requested PD k-steps ahead of their MFMAs (about six 1 KiB fragments in
 // flight per wave); a scheduling fence per step keeps the compiler from
-// hoisting further loads.
-template <class AT, int RBk, int MPW, int NKF, int INFL, int NP, class GCB>
-__device__ __forceinline__ void gemm_run(f32x4 (&acc)[MPW][RBk], const AT* A, int lda, const uint4* W, int KBT,
-                                         int kf0, GCB gcb, int lane, uint4 (&bc)[NP][MPW]) {
+// hoisting further loads.  (The products outside the layers: observation
+// tokens and their keys and values.)
+template <class AT, int RBk, int MPW, int NKF, class GCB>
+__device__ __forceinline__ void gemm_acc(f32x4 (&acc)[MPW][RBk], const AT* A, int lda, const uint4* W, int KBT,
+                                         int kf0, GCB gcb, int lane) {
   using O = Op<AT>;
-  constexpr int PD = pd_of<MPW, NKF, INFL>();
-  static_assert(NP >= 1 && NP <= PD, "prefetched k-steps");
+  constexpr int PD0 = 6 / MPW > 0 ? 6 / MPW : 1, PD = PD0 < NKF ? PD0 : (NKF > 1 ? NKF - 1 : 1);
   const int lc = lane & 15, lq = lane >> 4;
   const uint4* wp[MPW];
 #pragma unroll
   for (int m = 0; m < MPW; ++m) wp[m] = W + ((size_t)gcb(m) * KBT + kf0) * 64 + lane;
   uint4 buf[PD + 1][MPW];
 #pragma unroll
-  for (int d = 0; d < NP; ++d)
-#pragma unroll
-    for (int m = 0; m < MPW; ++m) buf[d][m] = bc[d][m];
-#pragma unroll
-  for (int d = NP; d < PD; ++d)
+  for (int d = 0; d < PD; ++d)
 #pragma unroll
     for (int m = 0; m < MPW; ++m)
       if (d < NKF) buf[d][m] = wp[m][d * 64];
@@ -246,14 +216,6 @@ __device__ __forceinline__ void gemm_run(f32x4 (&acc)[MPW][RBk], const AT* A, in
       for (int rb = 0; rb < RBk; ++rb) O::mma(acc[m][rb], buf[kf % (PD + 1)][m], a[rb]);
     __builtin_amdgcn_sched_barrier(0);
   }
-}
-
-template <class AT, int RBk, int MPW, int NKF, class GCB>
-__device__ __forceinline__ void gemm_acc(f32x4 (&acc)[MPW][RBk], const AT* A, int lda, const uint4* W, int KBT,
-                                         int kf0, GCB gcb, int lane) {
-  uint4 bc[1][MPW];
-  gemm_pref<1, MPW>(bc, W, KBT, kf0, gcb, lane);
-  gemm_run<AT, RBk, MPW, NKF, 6, 1>(acc, A, lda, W, KBT, kf0, gcb, lane, bc);
 }
 
 // a value every lane of the wave holds alike, as a scalar
@@ -639,7 +601,7 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
       f32x4 kv[MPWK][1];
 #pragma unroll
       for (int m = 0; m < MPWK; ++m) kv[m][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-      gemm_acc<AT, 1, MPWK, D / O::KF>(kv, xa, LDA, p.pk + p.poff[l].kv, D / O::KF, 0,
+      gemm_acc<AT, 1, MPWK, D / O::KF>(kv, xa, LDA, p.pk + p.loff[l].pk_kv, D / O::KF, 0,
                                         [&](int m) { return w + NW * m; }, lane);
       const uint32_t bkv = p.loff[l].b_kv;
 #pragma unroll
@@ -1798,7 +1760,7 @@ __global__ void __launch_bounds__(512) obs_fold_kernel(const KParams p) {
   f32x4 kv[MPWK][1];
 #pragma unroll
   for (int m = 0; m < MPWK; ++m) kv[m][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-  gemm_acc<AT, 1, MPWK, D / O::KF>(kv, xa, LDA, p.pk + p.poff[l].kv, D / O::KF, 0,
+  gemm_acc<AT, 1, MPWK, D / O::KF>(kv, xa, LDA, p.pk + lo.pk_kv, D / O::KF, 0,
                                     [&](int m) { return w + NW * m; }, lane);
 #pragma unroll
   for (int m = 0; m < MPWK; ++m) {
@@ -2003,6 +1965,22 @@ bool kernel_available(const KernelKey& key, int* threads) {
   if (EVO_MATCH(AT, D, DH, HZ, SPT, DFF, TEAM)) {          \
     if (threads) *threads = NW * 64;                       \
     return true;                                           \
+  }
+  EVO_SHAPES(X)
+#undef X
+  return false;
+}
+
+bool kernel_layer_layout(const KernelKey& key, LayerLayout* out) {
+#define X(AT, D, DH, HZ, SPT, DFF, NW, HG, FC, SMAX, TEAM)                                                        \
+  if (EVO_MATCH(AT, D, DH, HZ, SPT, DFF, TEAM)) {                                                                 \
+    using C = Cfg<AT, D, DH, HZ, SPT, DFF, NW, HG, FC, SMAX, TEAM>;                                               \
+    *out = LayerLayout{{C::pLN1, C::pLN1 + D, C::pBQKV, C::pBO, C::pLN2, C::pLN2 + D, C::pBQ, C::pBO2, C::pLN3,   \
+                        C::pLN3 + D, C::pB1, C::pB2},                                                             \
+                       C::PLAYER,                                                                                 \
+                       {C::off1(0), C::off2(0), C::off1(1), C::off2(1), C::off1(2), C::off2(2)},                  \
+                       C::LAYER};                                                                                 \
+    return true;                                                                                                  \
   }
   EVO_SHAPES(X)
 #undef X

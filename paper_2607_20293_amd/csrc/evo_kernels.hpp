@@ -18,17 +18,26 @@ struct DeviceGuard {
   }
 };
 
-// Float offsets (into the fp32 parameter copy) of one layer's small tensors.
+// Where the kernels that project the observation tokens (and fold them) find
+// a layer's tensors: float offsets into the fp32 parameter copy, and the
+// packed W_kv in 16-byte units.  The denoising kernel addresses everything
+// else by LayerLayout.
 struct LayerOff {
-  uint32_t ln1_g, ln1_b, b_qkv, b_o, ln2_g, ln2_b, b_q, b_kv, b_o2, ln3_g, ln3_b, b_1, b_2;
+  uint32_t b_q, b_kv;
   uint32_t w_q;    // W_q [d][d] (fp32 parameters), folded cross-attention only
   uint32_t w_o2t;  // W_o2 transposed [d][d] (appended to the fp32 parameters), folded only
-  uint32_t pad_;
+  uint64_t pk_kv;
 };
 
-// Offsets (in 16-byte units) of one layer's packed matrices.
-struct PackOff {
-  uint64_t qkv, o, q, kv, o2, w1, w2, pad_;
+// The layout of a layer that the denoising kernel is compiled for: float
+// offsets of its small tensors from the layer's first parameter (ln1 gain,
+// ln1 shift, b_qkv, b_o, ln2 gain, shift, b_q, b_o2, ln3 gain, shift, b_1,
+// b_2) and the layer's parameter count; offsets of its packed matrices in
+// bytes from the layer's first (qkv, o, q, o2, w1, w2) and their size.  A
+// policy is created only if its parameters lie like this.
+struct LayerLayout {
+  uint32_t small[12], floats;
+  uint32_t packed[6], packed_bytes;
 };
 
 struct KParams {
@@ -36,13 +45,12 @@ struct KParams {
   const float* raw;          // fp32 parameters (flat order of evo.h)
   const uint4* pk;           // packed projection matrices
   const LayerOff* loff;      // [L]
-  const PackOff* poff;       // [L]
   uint64_t pk_layers;        // fragment offset of layer 0 (layers are contiguous, each qkv, o, q, kv, o2, w1, w2)
   uint64_t pk_obs;           // fragment offset of W_obs (K padded to obs_pad)
   uint64_t pk_win;           // fp32 fragments of W_in (K = action_dim padded to 16)
   uint64_t pk_wout;          // fp32 fragments of W_out (rows padded to 16)
   uint32_t raw_layers;       // float offset of layer 0 in raw
-  uint32_t W_in, b_in, P_act, b_obs, P_mem, lnf_g, lnf_b, W_out, b_out, pad_;
+  uint32_t b_in, P_act, b_obs, P_mem, lnf_g, lnf_b, b_out;
   const float* tkv;          // [T][L][2d] time-token keys/values, indexed by timestep k
   const float* ddpm;         // [T][8] sampler constants by timestep k: sqrt(1-abar), 1/sqrt(abar), c0, ct, sigma
   const int32_t* tile_sample;  // [n_tiles][spt] sample index or -1
@@ -54,11 +62,11 @@ struct KParams {
   float* okv;                // [batch][L][n_obs][2d] observation-token keys/values
   float* cache;              // [n_tiles * team][3L][rows*d] per-workgroup residual caches
   float* acts;               // optional [batch][3L][T][H][d] record of evaluated residuals (else null)
-  float* xchg;               // [n_tiles][3][team][rows*d] partial residuals of team members
+  float* xchg;               // [n_tiles][kernel_team_slots][rows*d] partial residuals of team members
   unsigned* tctr;            // [n_tiles][16] team barrier counters (zeroed before each launch)
   unsigned* derr;            // device error flag (team barrier timed out)
   size_t okv_member_stride;  // floats between team members' observation key/value copies
-  int batch, team;
+  int batch;
   unsigned spin_limit;       // polls before a team wait gives up (sets *derr)
   int withhold;              // test hook: team member 0 never publishes its partials
   int fold;                  // cross-attention folded: okv holds fold records [batch][L][n_obs][2 NH d + 16]
@@ -72,6 +80,8 @@ struct KernelKey {
 
 // Returns true and the workgroup size if `key` is compiled.
 bool kernel_available(const KernelKey& key, int* threads);
+// The layer layout `key` is compiled for (false: not compiled).
+bool kernel_layer_layout(const KernelKey& key, LayerLayout* out);
 // Largest supported action_dim (all shapes) and n_obs_tokens (per shape).
 int kernel_max_action_dim();
 int kernel_max_obs_tokens_for(const KernelKey& key);
