@@ -129,7 +129,9 @@ typedef struct evo_policy evo_policy;
 int64_t evo_weight_count(const evo_policy_desc* desc);
 
 /* Validate a descriptor without creating anything (host-only).  Returns
- * EVO_OK, EVO_E_INVALID or EVO_E_UNSUPPORTED (shape not compiled). */
+ * EVO_OK, EVO_E_INVALID or EVO_E_UNSUPPORTED (shape not compiled);
+ * EVO_E_STATE if the library's parameter layout is not the one its kernels
+ * are compiled for (a fault of the build, also checked at creation). */
 int evo_check_desc(const evo_policy_desc* desc);
 
 /* Create a policy on the current HIP device.

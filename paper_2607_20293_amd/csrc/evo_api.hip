@@ -170,6 +170,50 @@ struct evo_policy {
   int64_t t_n = 0;
 };
 
+// Packed projection matrices (in 16-byte units): the size of one, and where
+// those of layer l lie if the layers begin at `first`.
+static uint64_t pack_units(const Shape& s, int N, int Kpad) {
+  return (uint64_t)(N / 16) * (Kpad / (s.dtype == EVO_BF16 ? 32 : 16)) * 64;
+}
+struct PackOff {
+  uint64_t qkv, o, q, kv, o2, w1, w2;
+};
+static PackOff pack_layer(const Shape& s, uint64_t first, int l) {
+  const uint64_t dd = pack_units(s, s.d, s.d), df = pack_units(s, s.dff, s.d);
+  PackOff po;
+  po.qkv = first + l * (8 * dd + 2 * df);
+  po.o = po.qkv + 3 * dd;
+  po.q = po.o + dd;
+  po.kv = po.q + dd;
+  po.o2 = po.kv + 2 * dd;
+  po.w1 = po.o2 + dd;
+  po.w2 = po.w1 + df;
+  return po;
+}
+
+// The denoising kernel addresses the layers at compile-time offsets: the flat
+// parameter order and the packing order must be these.
+static int check_layout(const Shape& s, const WeightOffsets& wo) {
+  for (int spt : {1, 2}) {
+    LayerLayout want;
+    if (!kernel_layer_layout(KernelKey{s.d, s.dh(), s.H, s.dff, s.dtype, spt, 1}, &want)) continue;
+    for (int l = 0; l < s.L; ++l) {
+      const auto& y = wo.layer[l];
+      const PackOff po = pack_layer(s, 0, l);
+      const size_t at[13] = {y.ln1_g, y.ln1_b, y.b_qkv, y.b_o, y.ln2_g, y.ln2_b, y.b_q, y.b_o2, y.ln3_g, y.ln3_b, y.b_1, y.b_2,
+                             l + 1 < s.L ? wo.layer[l + 1].ln1_g : wo.lnf_g};
+      const uint64_t mat[7] = {po.qkv, po.o, po.q, po.o2, po.w1, po.w2, pack_layer(s, 0, l + 1).qkv};
+      const size_t base = wo.layer[0].ln1_g + (size_t)l * want.floats;
+      const uint64_t pbase = (uint64_t)l * want.packed_bytes;
+      bool same = at[12] == base + want.floats && mat[6] * 16 == pbase + want.packed_bytes;
+      for (int i = 0; i < 12; ++i) same = same && at[i] == base + want.small[i];
+      for (int i = 0; i < 6; ++i) same = same && mat[i] * 16 == pbase + want.packed[i];
+      if (!same) return fail(EVO_E_STATE, "the parameters of layer %d do not lie as the kernel is compiled for", l);
+    }
+  }
+  return EVO_OK;
+}
+
 // Where evo_denoise_noalloc's working data lie in its array, and their size.
 struct ScratchLayout {
   size_t plan, cache, okv, xchg, ctr, total;
@@ -265,7 +309,8 @@ int evo_check_desc(const evo_policy_desc* desc) {
   Shape s;
   int rc = shape_from_desc(desc, &s);
   if (rc) return rc;
-  return check_supported(s);
+  if ((rc = check_supported(s))) return rc;
+  return guarded([&]() -> int { return check_layout(s, weight_offsets(s)); });
 }
 
 int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, size_t n_floats, evo_policy** out) {
@@ -307,7 +352,6 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
     } while (0)
 
     const int L = s.L, d = s.d, T = s.T, U = s.U();
-    const int KF = s.dtype == EVO_BF16 ? 32 : 16;
     // fp32 parameter copy (biases, norms, embeddings, head, and the source of the packed matrices)
     // (folded cross-attention: followed by the transpose of every layer's W_o2)
     const bool fold = s.folds_ca();
@@ -327,7 +371,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
     }
 
     // packed projection matrices
-    auto frag16 = [&](int N, int Kpad) { return (uint64_t)(N / 16) * (Kpad / KF) * 64; };
+    auto frag16 = [&](int N, int Kpad) { return pack_units(s, N, Kpad); };
     p->obs_pad = (s.obs_dim + 63) / 64 * 64;
     uint64_t off = 0;
     p->pk_obs = off;
@@ -337,41 +381,12 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
     off += (uint64_t)(d / 16) * 1 * 64;
     p->pk_wout = off;
     off += (uint64_t)1 * (d / 16) * 64;
-    struct PackOff {
-      uint64_t qkv, o, q, kv, o2, w1, w2;
-    };
-    std::vector<PackOff> pack(L);
     p->pk_layers = off;
-    for (int l = 0; l < L; ++l) {
-      PackOff& po = pack[l];
-      po.qkv = off; off += frag16(3 * d, d);
-      po.o = off; off += frag16(d, d);
-      po.q = off; off += frag16(d, d);
-      po.kv = off; off += frag16(2 * d, d);
-      po.o2 = off; off += frag16(d, d);
-      po.w1 = off; off += frag16(s.dff, d);
-      po.w2 = off; off += frag16(d, s.dff);
-    }
-    // the kernel addresses the layers at compile-time offsets: they must be these
-    for (int spt : {1, 2}) {
-      LayerLayout want;
-      if (!kernel_layer_layout(KernelKey{d, s.dh(), s.H, s.dff, s.dtype, spt, 1}, &want)) continue;
-      for (int l = 0; l < L; ++l) {
-        const auto& y = wo.layer[l];
-        const PackOff& po = pack[l];
-        const size_t at[13] = {y.ln1_g, y.ln1_b, y.b_qkv, y.b_o, y.ln2_g, y.ln2_b, y.b_q, y.b_o2, y.ln3_g, y.ln3_b, y.b_1, y.b_2,
-                               l + 1 < L ? wo.layer[l + 1].ln1_g : y.ln1_g + want.floats};
-        const uint64_t mat[7] = {po.qkv, po.o, po.q, po.o2, po.w1, po.w2, l + 1 < L ? pack[l + 1].qkv : off};
-        const size_t base = wo.layer[0].ln1_g + (size_t)l * want.floats;
-        const uint64_t pbase = p->pk_layers * 16 + (uint64_t)l * want.packed_bytes;
-        bool same = at[12] == base + want.floats && mat[6] * 16 == pbase + want.packed_bytes;
-        for (int i = 0; i < 12; ++i) same = same && at[i] == base + want.small[i];
-        for (int i = 0; i < 6; ++i) same = same && mat[i] * 16 == pbase + want.packed[i];
-        if (!same) {
-          release(p);
-          return fail(EVO_E_STATE, "the parameters of layer %d do not lie as the kernel is compiled for", l);
-        }
-      }
+    const auto pack = [&](int l) { return pack_layer(s, p->pk_layers, l); };
+    off = pack(L).qkv;
+    if ((rc = check_layout(s, wo))) {
+      release(p);
+      return rc;
     }
     CREATE_TRY(hipMalloc(&p->d_pk, off * sizeof(uint4)));
     CREATE_TRY(launch_pack(p->d_raw, wo.W_obs, d, d, s.obs_dim, p->obs_pad, s.dtype, p->d_pk + p->pk_obs, 0));
@@ -379,7 +394,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
     CREATE_TRY(launch_pack(p->d_raw, wo.W_out, 16, s.A, d, d, EVO_FP32, p->d_pk + p->pk_wout, 0));
     for (int l = 0; l < L; ++l) {
       const auto& y = wo.layer[l];
-      const PackOff& po = pack[l];
+      const PackOff po = pack(l);
       CREATE_TRY(launch_pack(p->d_raw, y.W_qkv, 3 * d, 3 * d, d, d, s.dtype, p->d_pk + po.qkv, 0));
       CREATE_TRY(launch_pack(p->d_raw, y.W_o, d, d, d, d, s.dtype, p->d_pk + po.o, 0));
       CREATE_TRY(launch_pack(p->d_raw, y.W_q, d, d, d, d, s.dtype, p->d_pk + po.q, 0));
@@ -398,7 +413,7 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
       lo.b_kv = (uint32_t)y.b_kv;
       lo.w_q = (uint32_t)y.W_q;
       lo.w_o2t = fold ? (uint32_t)(tr_off + (size_t)l * d * d) : 0u;
-      lo.pk_kv = pack[l].kv;
+      lo.pk_kv = pack(l).kv;
       wkv[l] = (uint32_t)y.W_kv;
       bkv[l] = (uint32_t)y.b_kv;
     }
@@ -447,9 +462,10 @@ int evo_create_policy(const evo_policy_desc* desc, const float* host_weights, si
       // compiled size that fits being chosen.  With bf16 operands at width
       // 256 the automatic choice keeps only the smallest size: teams of 2
       // measured faster than teams of 4 at every batch (Push-T shape, 25%
-      // density: 3.57 and 3.63 ms at batch 1 and 64 against 3.65 and 4.06
-      // ms), while with fp32 operands teams of 4 are far ahead wherever they
-      // fit (6.7-6.8 ms against 9.3-9.5 ms up to batch 64).  At width 768
+      // density, the whole call: 3.35, 3.34, 3.35 and 3.41 ms at batch 1, 16,
+      // 32 and 64 against 3.36, 3.42, 3.53 and 3.64), while with fp32 operands
+      // teams of 4 are far ahead wherever they fit (5.4-5.6 ms against 7.0 up
+      // to batch 64).  At width 768
       // teams of 6 serve batches up to n_cu / 9: the members' exchange takes
       // longer the more teams share the memory (10% density, 6 against 2
       // members: batch 1 14.0 and 17.8 ms, 20 15.7 and 17.3, 26 16.5 and

@@ -341,3 +341,17 @@ def test_flops_kernel_of_folded_and_projected_cross_attention(name, n_obs):
     # the paper's convention is the same either way
     F = O.unit_flops(s)
     assert st["flops_cacheable"] == T * L * (F["SA"] + F["CA"] + F["FFN"])
+
+
+@pytest.mark.parametrize("shape,dtype", [(I.TINY, "fp32"), (I.TINY, "bf16"), (I.PUSHT, "fp32"), (I.PUSHT, "bf16"),
+                                         (I.IMAGE, "bf16"), (I.BIMANUAL, "bf16")])
+def test_parameters_lie_as_the_kernels_are_compiled_for(shape, dtype):
+    """The denoising kernel's compile-time offsets of a layer's weights and
+    small tensors against the flat parameter order and the packing order, for
+    every compiled shape (evo_check_desc refuses a mismatch), and the flat
+    order against the generator's layout."""
+    import ctypes
+    _lib_or_skip()
+    d = evo.make_desc(shape, dtype, 1, 1)
+    assert evo.lib().evo_check_desc(ctypes.byref(d)) == 0
+    assert evo.lib().evo_weight_count(ctypes.byref(d)) == I.n_weight_floats(shape)
