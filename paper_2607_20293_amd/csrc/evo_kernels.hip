@@ -82,6 +82,12 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 // group lq takes k = 16·lq + j at step j, so each lane reads 16 contiguous
 // floats of its row (four 16-byte LDS reads) instead of 16 strided ones, and
 // four independent accumulators shorten the dependent MFMA chain.
+// The order of the last sum is a choice among equals, made by its outcome:
+// with bf16 operands another rounding of a score travels through all later
+// steps, and the worst of the 128 samples of the width-768 batch moves with it
+// around the 3e-2 that the tests allow: 2.5e-2 from the exact chunk with this
+// order, 3.1e-2 with (a0 + a1) + (a2 + a3).  Neither is the more exact sum; the
+// samples' median is 1.1e-2.
 template <int DH>
 __device__ __forceinline__ f32x4 qk_tile(const float* qrow, const float* krow, int lq) {
   static_assert(DH % 64 == 0 || DH == 32, "head size");
@@ -629,11 +635,24 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
   // so that a sample's result does not depend on the batch.
   constexpr int CE = (sizeof(AT) == 2) ? 2 : 4;
   unsigned char* const cbase = reinterpret_cast<unsigned char*>(p.cache) + (size_t)(tile * TEAM + member) * U * (R * D) * CE;
-  // Team exchange slots: [tile][3][TEAM][R*D] floats, slot n % 3 carries
-  // the partials of the n-th evaluated unit.  A slot word that still holds
-  // the sentinel has not been written yet; every member resets its own slot
-  // of unit n-1 once it holds all partials of unit n (then every member has
-  // finished reading unit n-1), before its next use at unit n+2.
+  // Team exchange slots: [tile][XS][XM][R*D] floats, slot n % XS carries the
+  // n-th exchanged unit.  A slot word that still holds the sentinel has not
+  // been written yet.  Wave w of a member reads only words that wave w of
+  // another member writes, so the following holds wave by wave.
+  //  * Three slots (XM = TEAM partials): a member empties its slot of unit n-1
+  //    once it holds all partials of unit n.  A member publishes its partial
+  //    of unit n after it has read everything of unit n-1, so nobody reads the
+  //    slot any more.  Its next use is unit n+2, and its next reader polls it
+  //    only after reading this member's partial of unit n+1, which is stored
+  //    after the wait (vmcnt 0) for the emptying stores.
+  //  * Four slots (SCATTER; XM = TEAM partials and the sums): a member empties
+  //    its slot of unit n-2, and its own columns of that slot's sums, together
+  //    with the stores of its partial of unit n, before any of unit n is read.
+  //    It then holds all sums of unit n-1, each published by an owner that had
+  //    read everything of unit n-2, so nobody reads the slot any more.  Its
+  //    next use is unit n+2, and its next reader polls it only after reading
+  //    this member's partials and sums of unit n+1, stored after the wait for
+  //    the emptying stores.
   // SC1 cache-policy bit: device-coherent access; at width 768 also the
   // non-temporal bit, so that the exchange traffic (three 96 KiB slots per
   // member and unit) does not displace the weights from the L2
@@ -667,7 +686,7 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
     __builtin_amdgcn_raw_buffer_store_b128(v, xr, xoff(slot, m) + xcst(c, rb), 0, kCoherent);
   };
   if constexpr (TEAM > 1) {
-    // all three slots of this member start empty; one counter barrier makes
+    // all slots of this member start empty; one counter barrier makes
     // sure no member reads a slot before its owner has emptied it
     const u32x4 empty = {kEmpty, kEmpty, kEmpty, kEmpty};
 #pragma unroll
@@ -1429,7 +1448,7 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
             for (int rb = 0; rb < RB; ++rb)
               xstore(empty, prev, SCATTER && c / OWN == member ? TEAM : member, c, rb);
         };
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the reset of this slot (one unit ago) has landed
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the last emptying stores (this slot's among them, or sooner) have landed
         // (a word equal to the sentinel becomes the canonical NaN)
         const auto canonical = [&](f32x4 x) {
           u32x4 v = __builtin_bit_cast(u32x4, x);
@@ -1445,8 +1464,8 @@ __global__ void __launch_bounds__(NW * 64) denoise_kernel(const KParams p) {
             if (!(p.withhold && member == 0) && !(SCATTER && c / OWN == member))
               xstore(v, cur, member, c, rb);
           }
-        // (this unit was reached, so every member has read everything of the
-        // unit before the last)
+        // (this member holds all sums of the last unit, so every member has
+        // read everything of the one before)
         if constexpr (SCATTER) empty_prev();
         // bounded wait for every word of `v` (loaded by `load`) to be written;
         // polls back to back (each is a memory round trip), the error flag
