@@ -3,13 +3,17 @@
 // which the method leaves unchanged, Sec. 3.1 and Sec. 3.4).
 //
 // Activations are NHWC fp32 in HBM.  With bf16 operands, GroupNorm groups of
-// 16 channels and widths that are multiples of 64, every layer is one kernel
-// that keeps whole images on a workgroup (conv_gn_kernel, and stem_kernel for
-// the first layer and its pooling; see there).  512 frames of 84x84: 20
-// kernels, 755 us; the general path 41 kernels, 1490 us.
+// 16 channels, widths that are multiples of 64 and every map after the stem's
+// pooling 2 to 24 or so pixels wide (an arrangement of kFused for each layer,
+// see plan_fused; frames from about 33x33 to 100x100 with four stages), every
+// layer after the stem is one kernel that keeps whole images on a workgroup
+// (conv_gn_kernel).  With at most 4 image channels, frames at least 12 pixels
+// wide and a stem of a multiple of 64 channels that fits LDS, so are the stem
+// and its pooling (stem_kernel).  512 frames of 84x84: 20 kernels, 750 us with
+// other inputs for each call; the general path 41 kernels, 1490 us.
 //
-// The general path (fp32, other groups or widths, maps too large for LDS) is
-// the rest of this comment.  Convolutions are implicit GEMMs on
+// The general path (fp32, all other shapes; see also plan_layer) is the rest
+// of this comment.  Convolutions are implicit GEMMs on
 // MFMA: M = output pixels, N = output channels, K = kh * kw * Cin in
 // (kh, kw, Cin) order, which is the packed weight layout [Cout][Kp] (K
 // padded to the K step).  The A tile is gathered from the input with the
@@ -1114,9 +1118,9 @@ __global__ void pack_fused_kernel(const float* __restrict__ w, int Cout, int Cin
   X(7, 4, 4, 1, 1) X(9, 4, 4, 1, 1) X(4, 4, 2, 2, 1) X(8, 4, 1, 2, 2) X(9, 4, 1, 2, 2)            \
   X(5, 4, 1, 2, 2) X(5, 4, 1, 1, 4) X(4, 1, 8, 1, 1) X(5, 1, 8, 1, 1) X(2, 1, 4, 1, 2)            \
   X(3, 1, 4, 1, 2) X(2, 1, 4, 1, 1) X(3, 1, 4, 1, 1) X(3, 1, 1, 1, 4) X(3, 1, 1, 1, 2)            \
-  X(1, 1, 1, 1, 8) X(1, 1, 1, 1, 4) X(3, 2, 1, 2, 4) X(3, 2, 1, 2, 2) X(5, 2, 1, 2, 2)            \
-  X(7, 1, 4, 1, 1) X(9, 1, 4, 1, 1) X(4, 1, 2, 1, 1) X(8, 1, 1, 1, 2) X(9, 1, 1, 1, 2)            \
-  X(5, 1, 1, 1, 2) X(5, 1, 1, 1, 4)
+  X(1, 1, 1, 1, 8) X(1, 1, 1, 1, 4) X(3, 2, 1, 2, 2) X(5, 2, 1, 2, 2) X(7, 1, 4, 1, 1)            \
+  X(9, 1, 4, 1, 1) X(4, 1, 2, 1, 1) X(8, 1, 1, 1, 2) X(9, 1, 1, 1, 2) X(5, 1, 1, 1, 2)            \
+  X(5, 1, 1, 1, 4)
 constexpr int kSmallCalls = 7;
 
 struct FusedCfg {
@@ -1606,6 +1610,9 @@ hipError_t launch_stem(const evo_encoder* e, const ConvLayer& L, const float* im
 // Which layers run fused, and their plans.  Every layer after the stem, or
 // none (see conv_gn_kernel): bf16 operands, groups of 16 channels, and an
 // arrangement for every layer.  The stem too where the image fits LDS.
+// (84x84 frames, fused and general path: 2 frames 171 and 259 us, 100 frames
+// 392 and 511, 512 frames 695 and 1500; on an encoder for 512 frames 2 frames
+// 226 and 560 us, 64 frames 269 and 627.)
 void plan_encoder(evo_encoder* e, int n_cu) {
   const evo_encoder_desc& d = e->desc;
   e->fused = e->bf && d.gn_group == 16;
@@ -1830,11 +1837,13 @@ int evo_create_encoder(const evo_encoder_desc* desc, const float* host_weights, 
       off += 2 * (size_t)L.cout;
     }
     for (int i = 0; i < 4; ++i) ENC_TRY(hipMalloc(&e->buf[i], e->buf_floats * sizeof(float)));
-    ENC_TRY(hipMalloc(&e->ws, (size_t)kWsFloats * sizeof(float)));
-    ENC_TRY(hipMalloc(&e->zeros, 256));
-    ENC_TRY(hipMemset(e->zeros, 0, 256));
-    ENC_TRY(hipMalloc(&e->part, e->part_cap * sizeof(double2)));
-    ENC_TRY(hipMalloc(&e->shift, e->shift_cap * sizeof(float)));
+    if (!e->fused || !e->stem_nb) {  // some layer runs on the general path
+      ENC_TRY(hipMalloc(&e->ws, (size_t)kWsFloats * sizeof(float)));
+      ENC_TRY(hipMalloc(&e->zeros, 256));
+      ENC_TRY(hipMemset(e->zeros, 0, 256));
+      ENC_TRY(hipMalloc(&e->part, e->part_cap * sizeof(double2)));
+      ENC_TRY(hipMalloc(&e->shift, e->shift_cap * sizeof(float)));
+    }
     ENC_TRY(hipEventCreateWithFlags(&e->ev_done, hipEventDisableTiming));
     ENC_TRY(hipDeviceSynchronize());
 #undef ENC_TRY
