@@ -443,7 +443,7 @@ def main():
         collect_ms = ev[0].elapsed_time(ev[1]) / reps
         scores_ms = ev[1].elapsed_time(ev[2]) / reps
         U, T, V = 3 * s.n_layers, s.n_steps, s.horizon * s.d_model
-        gram_flops = 2.0 * R * U * T * T * V
+        gram_flops = 1.0 * R * U * T * (T + 1) * V  # the triangle that is multiplied (2 per multiply-add)
         extras["redundancy_pusht_fp32_r8"] = {
             "collect_ms": round(collect_ms, 4), "scores_ms": round(scores_ms, 4),
             "gram_TFLOPs": round(gram_flops / (scores_ms * 1e-3) / 1e12, 2),
