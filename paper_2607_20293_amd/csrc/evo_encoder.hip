@@ -1118,9 +1118,9 @@ __global__ void pack_fused_kernel(const float* __restrict__ w, int Cout, int Cin
   X(7, 4, 4, 1, 1) X(9, 4, 4, 1, 1) X(4, 4, 2, 2, 1) X(8, 4, 1, 2, 2) X(9, 4, 1, 2, 2)            \
   X(5, 4, 1, 2, 2) X(5, 4, 1, 1, 4) X(4, 1, 8, 1, 1) X(5, 1, 8, 1, 1) X(2, 1, 4, 1, 2)            \
   X(3, 1, 4, 1, 2) X(2, 1, 4, 1, 1) X(3, 1, 4, 1, 1) X(3, 1, 1, 1, 4) X(3, 1, 1, 1, 2)            \
-  X(1, 1, 1, 1, 8) X(1, 1, 1, 1, 4) X(3, 2, 1, 2, 2) X(5, 2, 1, 2, 2) X(7, 1, 4, 1, 1)            \
-  X(9, 1, 4, 1, 1) X(4, 1, 2, 1, 1) X(8, 1, 1, 1, 2) X(9, 1, 1, 1, 2) X(5, 1, 1, 1, 2)            \
-  X(5, 1, 1, 1, 4)
+  X(1, 1, 1, 1, 8) X(1, 1, 1, 1, 4) X(3, 2, 1, 2, 4) X(3, 2, 1, 2, 2) X(5, 2, 1, 2, 2)            \
+  X(7, 1, 4, 1, 1) X(9, 1, 4, 1, 1) X(4, 1, 2, 1, 1) X(8, 1, 1, 1, 2) X(9, 1, 1, 1, 2)            \
+  X(5, 1, 1, 1, 2) X(5, 1, 1, 1, 4)
 constexpr int kSmallCalls = 7;
 
 struct FusedCfg {

@@ -289,6 +289,8 @@ def test_encoder_plan_keeps_the_general_path_where_it_is_faster():
     for f in (I.EncoderShape(84, 84, gn_group=8), I.EncoderShape(84, 84, widths=(64, 128, 200, 512), gn_group=8),
               I.EncoderShape(120, 120), I.EncoderShape(32, 32)):
         assert not evo.encoder_plan(f, "bf16", 64, 64).any()
+    # a middle-sized map: 3 x 2 blocks a wave, two waves along the channels, four K shares
+    assert tuple(evo.encoder_plan(I.EncoderShape(48, 48), "bf16", 512, 100)[11]) == (200, 2, 4, 4)
     # in_ch beyond 4: an unfused stem before fused layers
     plan = evo.encoder_plan(I.EncoderShape(84, 84, in_ch=6), "bf16", 64, 64)
     assert not plan[0].any() and plan[1:, 0].all()
