@@ -950,9 +950,9 @@ __global__ void __launch_bounds__(WM * WN * WK * 64, MBW * NBW > 32 ? 1 : 2) con
 
   // ---- GroupNorm statistics of every image and group (mean, then the
   // squares around it).  In registers (one image a workgroup, also in the
-  // max_batch arrangement): a lane's rows, the wave's lanes, then the waves in order.  Else the channels
-  // of each row to LDS, 1 << tpl threads take every (1 << tpl)-th row of an
-  // image, and a tree adds the threads.
+  // max_batch arrangement): a lane's rows, the wave's lanes, then the waves in
+  // order.  Else the channels of each row to LDS, 1 << tpl threads take every
+  // (1 << tpl)-th row of an image, and a tree adds the threads.
   float* const smean = reinterpret_cast<float*>(lds + a.a_bytes);  // [NB][ipw]
   float* const srstd = smean + NB * a.ipw;
   const double inv_cnt = 1.0 / ((double)HW * 16.0);
@@ -1439,9 +1439,10 @@ ConvPlan plan_conv(int M, int Cout, int steps) {
 }
 
 // Cheapest wave arrangement of a fused layer for n images of H x W, with the
-// order of sums of `like` if given.  Cycles of a workgroup: matrix cores, its weight stream from L2 (48 bytes a cycle and
-// CU), its LDS reads, each shared by the workgroups that run on a CU at once;
-// plus staging and about 5000 for its start and statistics.
+// order of sums of `like` if given.  Cycles of a workgroup: matrix cores or its
+// LDS reads, shared by the workgroups that run on a CU at once; plus staging
+// and about 5000 for its start and statistics.  (The weight stream from L2 is
+// not counted.)
 bool plan_fused(int n, const ConvLayer& L, int H, int W, bool pool, int n_cu, const FusedPlan* like, FusedPlan* out) {
   const int Ho = out_size(H, L.k, L.stride, L.pad), Wo = out_size(W, L.k, L.stride, L.pad), HW = Ho * Wo;
   if ((L.k != 3 && L.k != 1) || L.cin % 64 || L.cout % 64 || Wo < 2 || HW < 2) return false;
@@ -1469,9 +1470,9 @@ bool plan_fused(int n, const ConvLayer& L, int H, int W, bool pool, int n_cu, co
       const long long occ = std::max(1ll, std::min((long long)kLdsBytes / lds, 8ll / waves));
       const double on = (double)std::min<long long>(occ, (wgs + n_cu - 1) / n_cu);  // workgroups that share a CU
       const double steps = (double)nit * S, one = f.mbw * f.nbw * 16.0 * steps;      // one wave's MFMAs
-      const double mf = std::max(one * waves * on / 4.0, one), l2 = 16.0 * nb * f.wm * L.K * 2 / 48.0 * on;
+      const double mf = std::max(one * waves * on / 4.0, one);
       const double ld = waves * steps * f.mbw * 8.0 * on, st = stage / 32.0 * nit * on;
-      const double cost = (double)((wgs + n_cu * occ - 1) / (n_cu * occ)) * (std::max({mf, l2, ld}) + st + 5000.0);
+      const double cost = (double)((wgs + n_cu * occ - 1) / (n_cu * occ)) * (std::max(mf, ld) + st + 5000.0);
       if (out->cfg < 0 || cost < best) {
         best = cost;
         *out = FusedPlan{c, ipw, PW, PP, nit, (int)a_bytes, (int)lds, in_regs};
